@@ -159,6 +159,145 @@ IncLayout inc_layout(uint32_t n, uint64_t cap, uint64_t maxc) {
 }
 uint32_t bit_length(uint32_t x) { return x ? 32u - (uint32_t)__builtin_clz(x) : 0u; }
 
+// Units of `g` whose order key exceeds K, or a few more: K is rounded down to the next threshold
+// kept (exact below kKeyExact, which covers every wave cap).
+uint32_t units_above(const rept_graph* g, uint64_t K) {
+    uint32_t lo = 0, hi = kKeyTab;  // last threshold <= K
+    while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (key_threshold(mid) <= K) lo = mid; else hi = mid;
+    }
+    return g->above[lo];
+}
+
+// Cut the jobs' units into the tiles of the two queues and fit the grids to them.
+// graph_of(j): the graph of job j.
+template <typename GraphOf>
+void plan_tiles(BatchHeader* h, JobDev* jobs, const GraphOf& graph_of, const rept_tuning* tu) {
+    // (an order key k stands for up to 9k + 7 lists; 8k is taken, the reverse lists' share)
+    uint64_t lists = 0;
+    for (uint32_t j = 0; j < h->njobs; ++j) lists += graph_of(j)->E + graph_of(j)->num_rev;
+    const uint32_t lblocks = h->split ? h->light_blocks : h->blocks;
+    const uint32_t lwaves = lblocks * ((h->split ? kLightThreads : h->threads) / 64);
+    // Lists per tile: a queue that hands each workgroup (wavefront) one tile ends unevenly, but a part
+    // of a unit stages the unit's list again and updates the counters of its entries again, most of
+    // them hubs' (one 64-byte line of counters takes an update every 12 ns).  2M-edge power law,
+    // m = 10, c = 30: 0.54 ms at one tile per team, 0.59 at 4 and 0.84 at 16 for the heavy queue; 0.55
+    // against 0.60 and 0.79 at 4 and 8 for the light one.  A light tile keeps 512 lists (one unit's,
+    // or several small units') so that a lone wavefront is not left with eight units of 583.
+    const uint64_t hl = std::max<uint64_t>(lists / h->blocks, 1024);
+    const uint64_t ll = std::max<uint64_t>(512, std::min<uint64_t>(lists / lwaves, 4096));
+    uint32_t qmax = 0;  // log2 of the units per light tile, at most
+    while (qmax < kLightOne && (2u << qmax) <= h->light_tile) ++qmax;
+    uint64_t hp = 0, lp = 0;
+    for (uint32_t j = 0; j < h->njobs; ++j) {
+        JobDev& d = jobs[j];
+        const rept_graph* g = graph_of(j);
+        auto units_in = [&](uint64_t K) {  // units of the job's range with key > K
+            const uint32_t a = units_above(g, K);
+            return std::min(a, d.unit1) - std::min(std::min(a, d.unit1), d.unit0);
+        };
+        const uint32_t nh = units_in(h->wave_cap), nu = d.unit1 - d.unit0;
+        d.hcls[0] = nh;
+        for (uint32_t k = 1; k < kHeavyClasses; ++k)
+            d.hcls[k] = std::min(d.hcls[k - 1], units_in(std::max<uint64_t>(h->wave_cap, (hl << (k - 1)) / 8)));
+        // class i or above: a unit's lists exceed ll / 2^(kLightOne - i + 1) (ll 2^(i - kLightOne - 1))
+        for (uint32_t i = 0; i < kLightClasses; ++i) {
+            const uint32_t a = i + qmax <= kLightOne ? nu
+                                                     : units_in((i > kLightOne ? ll << (i - kLightOne - 1)
+                                                                               : ll >> (kLightOne - i + 1)) / 8);
+            d.lcls[i] = a > nh ? a - nh : 0u;
+            if (i) d.lcls[i] = std::min(d.lcls[i], d.lcls[i - 1]);
+        }
+        uint64_t ht = d.hcls[0], lt = 0;
+        for (uint32_t k = 1; k < kHeavyClasses; ++k) ht += (uint64_t)d.hcls[k] << (k - 1);
+        for (uint32_t i = 0; i < kLightClasses; ++i) {
+            const uint64_t c = d.lcls[i] - (i + 1 < kLightClasses ? d.lcls[i + 1] : 0u);
+            lt += i > kLightOne ? c << (i - kLightOne) : (c + (1u << (kLightOne - i)) - 1) >> (kLightOne - i);
+        }
+        d.heavy_prefix = (uint32_t)hp;
+        d.light_prefix = (uint32_t)lp;
+        hp += ht;
+        lp += lt;
+    }
+    h->heavy_total = (uint32_t)hp;
+    h->light_total = (uint32_t)lp;
+    if (!(tu && tu->blocks)) {
+        const uint64_t waves = h->threads / 64;
+        const uint64_t need = std::max<uint64_t>(hp, h->split ? 0 : (lp + waves - 1) / waves);
+        h->blocks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(h->blocks, need));
+        if (h->split) {
+            const uint64_t lw = kLightThreads / 64;
+            h->light_blocks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(h->light_blocks, (lp + lw - 1) / lw));
+        }
+    }
+    // the preparing kernel: enough workgroups to clear the outputs and to write the tables
+    uint64_t pb = h->any_zero ? std::min<uint64_t>(1024, (h->zero_words + 1023) / 1024) : 1;
+    if (h->any_fill)
+        pb = std::max<uint64_t>(pb, std::max<uint64_t>(std::min<uint64_t>(1024, (h->fill_edges + 255) / 256),
+                                                       std::min<uint64_t>(8192, (h->fill_edges + 4095) / 4096)));
+    // (sized for the largest job; a batch's other jobs leave their share of them idle)
+    if (h->njobs > 1) pb = std::min<uint64_t>(pb, std::max<uint64_t>((h->fill_edges + 4095) / 4096, 4096 / h->njobs));
+    h->prep_blocks = (uint32_t)std::max<uint64_t>(1, pb);
+}
+
+// Whether a shape the caller chose is within the declared budget: per staged entry of a unit's list
+// 6 bytes for each of two hash slots (four in the light phase, if they fit) and 8 + 2 gs + 4 G, per
+// staged list 16 + 2 gs + 4 G, 12 + 8 G more each with Algorithm 2's counters, and per wavefront 2.8 KB
+// and the processors' counts, in the 160 KB of a compute unit.  The kernel's own areas
+// (rept_count_lds) are smaller almost everywhere; the budget stays what it was so that a tuned shape
+// is accepted or refused as before.
+uint32_t budget_area(uint32_t DW, uint32_t DB, uint32_t G, uint32_t gs, uint32_t table, bool eta) {
+    uint32_t H = 64, p = 0;
+    while (H < table * DW) H <<= 1;
+    auto add = [&](uint32_t bytes) { p = (p + bytes + 15u) & ~15u; };
+    for (uint32_t b : {4 * H, 2 * H, 4 * DW, 4 * DW, 2 * gs * DW, 4 * G * DW, 4 * DB, 4 * DB, 2 * gs * DB, 4 * G * DB,
+                       8 * (DB + 1)})
+        add(b);
+    if (eta)
+        for (uint32_t b : {4 * DB, 4 * G * DW, 4 * G * DB}) add(b);
+    add(256);
+    return p;
+}
+bool shape_allowed(const rept_tuning* tu, uint32_t wave_cap, uint32_t block_cap, uint32_t b_chunk, uint32_t threads,
+                   uint32_t G, uint32_t gs, uint32_t hist_c, bool split, bool wide, bool eta) {
+    const uint32_t cap = 160 * 1024 - 256;
+    const uint32_t misc = 256 + 4 * 320 + 4 * 320 + ((4 * hist_c + 15u) & ~15u) + 16;
+    uint32_t lthreads = threads, table = 4, lb = wave_cap;
+    if (split && wide) {
+        lthreads = 256;
+        table = 2;
+        lb = wave_cap < 128 ? wave_cap : 128u;
+    }
+    auto light = [&]() { return lthreads / 64 * (misc + budget_area(wave_cap, lb, G, gs, table, eta)); };
+    while (light() > cap) {
+        if (table == 4) {
+            table = 2;
+        } else if (!tu->wave_cap && wave_cap > 64) {
+            wave_cap >>= 1;
+            lb = lb < wave_cap ? lb : wave_cap;
+        } else {
+            return false;
+        }
+    }
+    auto heavy = [&]() {
+        const uint32_t nw = threads / 64, h = budget_area(block_cap, b_chunk, G, gs, 2, eta);
+        const uint32_t l = split ? 0u : nw * budget_area(wave_cap, lb, G, gs, table, eta);
+        return nw * misc + (h > l ? h : l);
+    };
+    while (threads <= 512 && heavy() > 80 * 1024 - 256 &&
+           ((!tu->b_chunk && b_chunk > 128) || (!tu->block_cap && block_cap > 1024))) {
+        if (!tu->b_chunk && b_chunk > 128) b_chunk >>= 1;
+        else block_cap >>= 1;
+    }
+    while (heavy() > cap) {
+        if (!tu->b_chunk && b_chunk > 128) b_chunk >>= 1;
+        else if (!tu->block_cap && block_cap > 64) block_cap >>= 1;
+        else return false;
+    }
+    return true;
+}
+
 // Fill the launch shape for jobs of at most G_max groups, at most c_max processors and at most
 // max_out entries in an apex list.
 rept_status make_header(uint32_t njobs, uint32_t G_max, uint32_t gs_max, uint32_t c_max, uint32_t max_out,
@@ -173,20 +312,17 @@ rept_status make_header(uint32_t njobs, uint32_t G_max, uint32_t gs_max, uint32_
     while (fit < max_out && fit < 2048) fit <<= 1;
     const bool own_block_cap = tu && tu->block_cap, own_b_chunk = tu && tu->b_chunk;
     uint32_t block_cap = own_block_cap ? tu->block_cap : fit;
-    // Lists of more than 1024 entries: one workgroup of 1024 threads per compute unit (16 waves),
-    // one 2048-entry table chunk (no second walk of a unit's B lists below 2048 entries),
-    // 1024-list B chunks, and units of up to 256 entries left to single wavefronts, taken 16 at a
-    // time (R-MAT scale 24, longest list 1761: 198 ms with units of up to 128 entries on
-    // wavefronts, 210 with up to 64; 274 with 512-thread workgroups, 1024-entry table chunks and
-    // 256-list B chunks, two workgroups per compute unit; 206 with 512-list B chunks.  With the
-    // four-slot heavy tables below: 179.9 ms at 128, 176.4 at 256, 175.6 at 256 with 16-unit
-    // light tiles).  Shorter lists keep 256-thread workgroups (the 1M/20M power-law graph,
-    // longest list 480: 5.99 ms; 8.5-10.8 with 1024 threads).
+    // Lists of more than 1024 entries: one workgroup of 1024 threads per compute unit (16 waves), one
+    // 2048-entry table chunk (no second walk of a unit's B lists below 2048 entries), 64 lists per
+    // wavefront and chunk, and units of up to 256 entries left to single wavefronts (R-MAT scale 24,
+    // longest list 1761: 166 ms, 176 with units of up to 96 entries on wavefronts, 204 with up to 48).
+    // Shorter lists keep 256-thread workgroups and units of up to 64 entries (the 1M/20M power-law
+    // graph, longest list 480: 4.6 ms; 4.9 with units of up to 48 or 96 entries on wavefronts).
     const bool wide = !own_block_cap && block_cap >= 2048 && !(tu && tu->threads);
     const bool own_wave_cap = tu && tu->wave_cap;
     uint32_t wave_cap = own_wave_cap ? tu->wave_cap : (wide ? 256u : 64u);
-    // units with long lists also have many lists to walk: bigger B chunks pay there, not on
-    // shorter lists (the 1M/20M power-law graph: 6.64 ms at 128, 7.13 at 64, 7.41 at 256)
+    // lists per chunk over the workgroup's wavefronts: 64 each where LDS is not what limits the
+    // resident wavefronts, 32 with shorter lists
     uint32_t b_chunk = own_b_chunk ? tu->b_chunk : (wide ? 1024u : (block_cap >= 2048 ? 512u : 128u));
     const uint32_t threads = (tu && tu->threads) ? tu->threads : (wide ? 1024u : 256u);
     const uint32_t light_tile = (tu && tu->light_tile) ? tu->light_tile : (wide ? 16u : 8u);
@@ -199,37 +335,25 @@ rept_status make_header(uint32_t njobs, uint32_t G_max, uint32_t gs_max, uint32_
     if (pl > 3 || (tu && tu->reserved)) return REPT_EINVAL;
     // default (0): the light phase in a launch of its own, on a second stream
     const bool split = pl != 1;
-    // A light launch of its own needs no heavy team area, and a heavy launch then needs no light
-    // areas.  It keeps the heavy launch's workgroup size, except with the wide shape below.
-    uint32_t light_threads = threads;
     const uint32_t hist_c = c_max <= REPT_HIST_CAP ? c_max : 0;
-    // the light phase's hash tables are sparser (fewer probes) where the LDS budget allows
-    uint32_t light_table = 4, heavy_table = 2;
-    // a light wavefront stages its lists to walk in chunks of light_b (at most wave_cap)
-    uint32_t light_b = wave_cap;
-    // The wide shape's light launch (units of up to 256 entries): 256-thread workgroups with
-    // two-slot tables and 128-list chunks, so that three fit a CU (12 waves); four-slot tables
-    // and 256-list chunks fit two (R-MAT scale 24: 169.8 against 175.9 ms; 64-list chunks 170.3)
-    if (split && wide) {
-        light_threads = 256;
-        light_table = 2;
-        light_b = wave_cap < 128 ? wave_cap : 128u;
-    }
+    // a light wavefront stages its lists to walk in chunks of light_b (one per lane at most)
+    uint32_t light_b = wave_cap < 64 ? wave_cap : 64u;
     auto heavy_lds = [&]() {  // the launch that runs the heavy phase (both phases if not split)
-        return rept_count_lds(threads, wave_cap, block_cap, b_chunk, G_max, gs_max, hist_c, light_table,
-                              heavy_table, light_b, eta, true, !split);
+        return rept_count_lds(threads, wave_cap, block_cap, b_chunk, G_max, gs_max, hist_c, light_b, eta, true,
+                              !split);
     };
     auto light_lds = [&]() {  // the light areas alone, in the launch that holds them
-        return rept_count_lds(split ? light_threads : threads, wave_cap, block_cap, b_chunk, G_max, gs_max, hist_c,
-                              light_table, heavy_table, light_b, eta, false, true);
+        return rept_count_lds(split ? kLightThreads : threads, wave_cap, block_cap, b_chunk, G_max, gs_max, hist_c,
+                              light_b, eta, false, true);
     };
-    // Past the 160 KB of a CU (static LDS takes a few bytes more), the light areas shrink first
-    // (sparser tables, then a default wave cap halved down to 64), then the default heavy chunk
-    // sizes.  A shape the caller chose is never changed: it is refused if it does not fit.
+    if (tu && !shape_allowed(tu, wave_cap, block_cap, b_chunk, threads, G_max, gs_max, hist_c, split, wide, eta))
+        return REPT_EINVAL;
+    // Past the 160 KB of a CU (static LDS takes a few bytes more), the light areas shrink first (fewer
+    // lists per chunk, then a default wave cap halved down to 64), then the default heavy chunk sizes.
     const uint32_t cap = 160 * 1024 - 256;
     while (light_lds() > cap) {
-        if (light_table == 4) {
-            light_table = 2;
+        if (light_b > 4) {
+            light_b >>= 1;
         } else if (!own_wave_cap && wave_cap > 64) {
             wave_cap >>= 1;
             light_b = light_b < wave_cap ? light_b : wave_cap;
@@ -250,22 +374,10 @@ rept_status make_header(uint32_t njobs, uint32_t G_max, uint32_t gs_max, uint32_
         else return REPT_EINVAL;
     }
     auto resident = [&](uint32_t bytes) {  // workgroups per CU, as the default grid counts them
-        uint32_t per_cu = rept_count_blocks_per_cu(threads, bytes, eta);
+        uint32_t per_cu = rept_count_blocks_per_cu(threads, bytes, eta, split ? 1u : 3u);
         if (per_cu == 0) per_cu = 1;
         return per_cu > 4 ? 4u : per_cu;
     };
-    // Sparser heavy tables (four slots per key: fewer probes past the first bucket) with the wide
-    // shape, where they fit and cost no resident workgroup (R-MAT scale 24, one 1024-thread
-    // workgroup per CU either way: 179 against 198 ms).  Shorter lists keep two: on the 1M/20M
-    // power-law graph four slots would drop REPT's default launch from four workgroups per CU to
-    // three (7.04 against 5.99 ms), and where they keep the occupancy they cost MASCOT with eight
-    // processors 9.8 against 8.0 ms, for 4.9 against 5.1 ms for REPT with the same m and c.
-    if (wide) {
-        const uint32_t per_cu2 = resident(heavy_lds());
-        heavy_table = 4;
-        const uint32_t lds4 = heavy_lds();
-        if (lds4 > cap || resident(lds4) < per_cu2) heavy_table = 2;
-    }
     const uint32_t lds = heavy_lds();
     uint32_t blocks = tu ? tu->blocks : 0;
     if (!blocks) blocks = resident(lds) * cus;
@@ -280,8 +392,6 @@ rept_status make_header(uint32_t njobs, uint32_t G_max, uint32_t gs_max, uint32_
     h->G_max = G_max;
     h->gs_max = gs_max;
     h->lds_bytes = lds;
-    h->light_table = light_table;
-    h->heavy_table = heavy_table;
     h->light_b = light_b;
     h->any_zero = any_zero ? 1u : 0u;
     h->any_eta = eta ? 1u : 0u;
@@ -289,9 +399,8 @@ rept_status make_header(uint32_t njobs, uint32_t G_max, uint32_t gs_max, uint32_
     h->split = split ? 1u : 0u;
     h->split_streams = (pl == 0 || pl == 3) ? 1u : 0u;
     if (h->split) {
-        h->light_threads = light_threads;
         h->light_lds = light_lds();
-        uint32_t per_cu = rept_count_blocks_per_cu(light_threads, h->light_lds, eta);
+        uint32_t per_cu = rept_count_blocks_per_cu(kLightThreads, h->light_lds, eta, 2);
         if (per_cu == 0) per_cu = 1;
         if (per_cu > 8) per_cu = 8;
         h->light_blocks = (tu && tu->blocks) ? tu->blocks : per_cu * cus;
@@ -315,6 +424,8 @@ rept_status make_job(const rept_job& jb, JobDev* d, uint64_t* zero_words) {
     d->roff = g->roff;
     d->rrec = g->rrec;
     d->rpos = g->rpos;
+    d->hubs = g->hubs;
+    d->n_hub = g->n_hub;
     d->global = jb.global;
     d->local = jb.local;
     group_params(jb.params.seed, G, d->hp);
@@ -402,6 +513,7 @@ rept_status count_one(const rept_graph* graph, const rept_params* params, uint64
             if (!check) continue;
             h.any_fill = 1;
             h.fill_edges = graph->E > UINT32_MAX ? UINT32_MAX : (uint32_t)graph->E;
+            plan_tiles(&h, &dq, [graph](uint32_t) { return graph; }, tuning);
             if (rept_launch_single(graph->ctrl, h, dq, (hipStream_t)stream) != hipSuccess) return REPT_EDEVICE;
         }
     }
@@ -765,6 +877,7 @@ rept_status rept_count_eta(const rept_graph* graph, const rept_params* params, i
             if (!check) continue;
             h.any_fill = 1;
             h.fill_edges = graph->E > UINT32_MAX ? UINT32_MAX : (uint32_t)graph->E;
+            plan_tiles(&h, &d, [graph](uint32_t) { return graph; }, tuning);
             if (rept_launch_zero(pairs, (uint64_t)8 * d.G * graph->E, s) != hipSuccess) return REPT_EDEVICE;
             if (rept_launch_single(graph->ctrl, h, d, s) != hipSuccess) return REPT_EDEVICE;
             if (rept_launch_eta(graph, d, eta, eta_v, (uint32_t)goff, c, s) != hipSuccess) return REPT_EDEVICE;
@@ -952,6 +1065,7 @@ rept_status rept_batch_prepare(const rept_job* jobs, uint32_t njobs, const rept_
     if (st != REPT_OK) return st;
     h.any_fill = any_fill ? 1u : 0u;
     h.fill_edges = fill_edges > UINT32_MAX ? UINT32_MAX : (uint32_t)fill_edges;
+    plan_tiles(&h, hj, [jobs](uint32_t j) { return jobs[j].graph; }, tuning);
     memcpy(host, &h, sizeof(h));
     // stream-ordered: launches enqueued on `stream` after this call see the table; the staging
     // buffer is reused only after this copy's event has completed

@@ -468,7 +468,7 @@ __global__ void k_slice_base(uint32_t* __restrict__ scount, const uint32_t* __re
 constexpr uint32_t PLACE_UNROLL = 4;
 // place the slice's entries in their segments (as k_scatter below, with LDS cursors); with
 // `rcnt`, also count the reverse pairs per target shard (the shard path of the reverse lists)
-constexpr uint32_t REV_BIT = 0x80000000u;
+constexpr uint32_t REV_BIT = REPT_REV_BIT;
 __global__ void __launch_bounds__(1024) k_slice_place(const OEntry* __restrict__ opart,
                                                       const uint32_t* __restrict__ boff, uint32_t nblk, uint32_t NB,
                                                       uint32_t shift, const uint32_t* __restrict__ slice_off,
@@ -556,7 +556,7 @@ __global__ void __launch_bounds__(1024) k_rev_part(const uint32_t* __restrict__ 
         const uint32_t a = rsrc[q];
         if (a == NO_EDGE) continue;
         const uint32_t b = nbr[q];
-        rpart[atomicAdd(&base[b >> shift], 1u)] = make_uint4(b, a, tim[q], (uint32_t)q);
+        rpart[atomicAdd(&base[b >> shift], 1u)] = make_uint4(b, a, tim[q] & ~REV_BIT, (uint32_t)q);
     }
 }
 
@@ -733,22 +733,27 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_classify(const uint32_t* __res
 // histogram apexes by unit key for the descending unit order (bucket n-1-key); needs the reverse
 // lists' offsets, and records their total
 __global__ void __launch_bounds__(SCAN_THREADS) k_apex_hist(const uint32_t* __restrict__ off,
-                                                            const uint32_t* __restrict__ roff, uint32_t n,
+                                                            const uint32_t* __restrict__ roff,
+                                                            const uint32_t* __restrict__ deg, uint32_t n,
                                                             uint32_t* ahist, BuildStats* st) {
-    __shared__ uint32_t h[APEX_LDS_BINS];
+    __shared__ uint32_t h[APEX_LDS_BINS], hd[kHubClasses];
     for (uint32_t i = threadIdx.x; i < APEX_LDS_BINS; i += blockDim.x) h[i] = 0;
+    for (uint32_t i = threadIdx.x; i < kHubClasses; i += blockDim.x) hd[i] = 0;
     __syncthreads();
     uint32_t a0, a1;
     node_range(n, a0, a1);
     for (uint32_t a = a0 + threadIdx.x; a < a1; a += blockDim.x) {
-        const uint32_t d = off[a + 1] - off[a];
+        const uint32_t d = off[a + 1] - off[a], dg = deg[a];
         if (d >= 2) {
             const uint32_t k = unit_key(off, roff, n, a);
             if (k < APEX_LDS_BINS) atomicAdd(&h[k], 1u);
             else atomicAdd(&ahist[n - 1 - k], 1u);
         }
+        if (dg >= (1u << kHubBits)) atomicAdd(&hd[hub_class(dg)], 1u);
     }
     __syncthreads();
+    for (uint32_t i = threadIdx.x; i < kHubClasses; i += blockDim.x)
+        if (hd[i]) atomicAdd(&st->dhist[i], hd[i]);
     for (uint32_t d = threadIdx.x; d < APEX_LDS_BINS; d += blockDim.x)
         if (h[d]) atomicAdd(&ahist[n - 1 - d], h[d]);
     if (blockIdx.x == 0 && threadIdx.x == 0) st->num_rev = roff[n];
@@ -757,9 +762,27 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_apex_hist(const uint32_t* __re
 // place apexes in out-degree-descending order: reserve each bin's range once per workgroup
 __global__ void __launch_bounds__(SCAN_THREADS) k_apex_scatter(const uint32_t* __restrict__ off,
                                                                const uint32_t* __restrict__ roff, uint32_t n,
+                                                               const uint32_t* __restrict__ deg,
                                                                const uint32_t* __restrict__ aoff, uint32_t* acur,
-                                                               uint32_t* apex) {
-    __shared__ uint32_t h[APEX_LDS_BINS];
+                                                               uint32_t* apex, uint32_t* hubs, BuildStats* st) {
+    __shared__ uint32_t h[APEX_LDS_BINS], from;
+    // the hubs are the nodes of degree class `from` or above: the lowest class from which there
+    // are at most kHubs of them (wavefront 0: three classes per lane, from the top)
+    static_assert(kHubClasses == 3 * 64, "three classes per lane");
+    if (threadIdx.x < 64) {
+        const uint32_t top = kHubClasses - 1 - 3 * threadIdx.x;
+        const uint32_t c0 = st->dhist[top], c1 = st->dhist[top - 1], c2 = st->dhist[top - 2];
+        const uint32_t before = wave_incl_scan(c0 + c1 + c2) - (c0 + c1 + c2);
+        const uint32_t ok = (before + c0 <= kHubs) + (before + c0 + c1 <= kHubs) + (before + c0 + c1 + c2 <= kHubs);
+        const uint32_t sum = wave_incl_scan(ok);
+        if (threadIdx.x == 63) from = kHubClasses - sum;
+    }
+    // aoff[n - 1 - k] counts the units whose key exceeds k (keys are at most n - 1)
+    if (blockIdx.x == 0)
+        for (uint32_t i = threadIdx.x; i < kKeyTab; i += blockDim.x) {
+            const uint32_t k = key_threshold(i);
+            st->above[i] = k < n ? aoff[n - 1 - k] : 0u;
+        }
     for (uint32_t i = threadIdx.x; i < APEX_LDS_BINS; i += blockDim.x) h[i] = 0;
     __syncthreads();
     uint32_t a0, a1;
@@ -775,7 +798,8 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_apex_scatter(const uint32_t* _
         if (h[k]) h[k] = aoff[n - 1 - k] + atomicAdd(&acur[n - 1 - k], h[k]);
     __syncthreads();
     for (uint32_t a = a0 + threadIdx.x; a < a1; a += blockDim.x) {
-        const uint32_t d = off[a + 1] - off[a];
+        const uint32_t d = off[a + 1] - off[a], dg = deg[a];
+        if (dg >= (1u << kHubBits) && hub_class(dg) >= from) hubs[atomicAdd(&st->n_hub, 1u)] = a;
         if (d < 2) continue;
         const uint32_t k = unit_key(off, roff, n, a);
         const uint32_t pos = k < APEX_LDS_BINS ? atomicAdd(&h[k], 1u)
@@ -808,7 +832,7 @@ __device__ __forceinline__ void emit_sorted(unsigned long long v, uint32_t idx, 
         const uint32_t b = (uint32_t)(v >> 32), t = (uint32_t)v & ~REV_BIT;
         const bool rev = ((uint32_t)v & REV_BIT) != 0;
         nbr[seg + idx] = b;
-        tim[seg + idx] = t;
+        tim[seg + idx] = (uint32_t)v;  // with the pair's REV_BIT
         if (R.src) R.src[seg + idx] = rev ? a : NO_EDGE;
         else if (rev) emit_rev(R, a, seg, d, idx, b, t);
     }
@@ -1357,10 +1381,11 @@ rept_status rept_build_impl(uint32_t n, const uint32_t* edges, uint64_t E, void*
         hipLaunchKernelGGL(k_rev_place, dim3((uint32_t)smax), dim3(1024), 0, s, (const uint4*)rpart, bscan, D.nblk,
                            D.NB, D.shift, slice_off, scount, off, rrec, rpos);
     }
-    hipLaunchKernelGGL(k_apex_hist, dim3(gA), dim3(256), 0, s, off, roff, n, ahist, st);
+    hipLaunchKernelGGL(k_apex_hist, dim3(gA), dim3(256), 0, s, off, roff, deg, n, ahist, st);
     if (scan_u32(ahist, n, part, aoff, s) != hipSuccess) return REPT_EDEVICE;
     hipLaunchKernelGGL(k_fill_u32, dim3(gN), dim3(256), 0, s, cursor, (uint64_t)n, 0u);
-    hipLaunchKernelGGL(k_apex_scatter, dim3(gA), dim3(256), 0, s, off, roff, n, aoff, cursor, apex);
+    hipLaunchKernelGGL(k_apex_scatter, dim3(gA), dim3(256), 0, s, off, roff, n, deg, aoff, cursor,
+                       apex, (uint32_t*)(P + L.ctrl + kHubOffset), st);
     if (hipGetLastError() != hipSuccess) return REPT_EDEVICE;
 
     BuildStats hs;
@@ -1388,6 +1413,9 @@ rept_status rept_build_impl(uint32_t n, const uint32_t* edges, uint64_t E, void*
     g->num_rev = hs.num_rev;
     g->work = hs.work;
     g->sum_out_sq = hs.sum_out_sq;
+    memcpy(g->above, hs.above, sizeof(g->above));
+    g->hubs = (const uint32_t*)(P + L.ctrl + kHubOffset);
+    g->n_hub = hs.n_hub;
     *out = g;
     return REPT_OK;
 }
