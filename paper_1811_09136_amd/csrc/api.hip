@@ -183,10 +183,12 @@ void plan_tiles(BatchHeader* h, JobDev* jobs, const GraphOf& graph_of, const rep
     // of a unit stages the unit's list again and updates the counters of its entries again, most of
     // them hubs' (one 64-byte line of counters takes an update every 12 ns).  2M-edge power law,
     // m = 10, c = 30: 0.54 ms at one tile per team, 0.59 at 4 and 0.84 at 16 for the heavy queue; 0.55
-    // against 0.60 and 0.79 at 4 and 8 for the light one.  A light tile keeps 512 lists (one unit's,
-    // or several small units') so that a lone wavefront is not left with eight units of 583.
+    // against 0.60 and 0.79 at 4 and 8 for the light one.  A light tile keeps 512 lists of small units, and
+    // a light unit is cut above 256 lists, so that a lone wavefront is not left with eight units of 583
+    // (10k nodes and 200k edges: a whole step of 482 us; 505 at 128 and 32, 555 at 512 and 64).
     const uint64_t hl = std::max<uint64_t>(lists / h->blocks, 1024);
-    const uint64_t ll = std::max<uint64_t>(512, std::min<uint64_t>(lists / lwaves, 4096));
+    const uint64_t lw = std::min<uint64_t>(lists / lwaves, 4096);
+    const uint64_t ll = std::max<uint64_t>(256, lw), lg = std::max<uint64_t>(512, lw);
     uint32_t qmax = 0;  // log2 of the units per light tile, at most
     while (qmax < kLightOne && (2u << qmax) <= h->light_tile) ++qmax;
     uint64_t hp = 0, lp = 0;
@@ -201,11 +203,11 @@ void plan_tiles(BatchHeader* h, JobDev* jobs, const GraphOf& graph_of, const rep
         d.hcls[0] = nh;
         for (uint32_t k = 1; k < kHeavyClasses; ++k)
             d.hcls[k] = std::min(d.hcls[k - 1], units_in(std::max<uint64_t>(h->wave_cap, (hl << (k - 1)) / 8)));
-        // class i or above: a unit's lists exceed ll / 2^(kLightOne - i + 1) (ll 2^(i - kLightOne - 1))
+        // class i or above: a unit's lists exceed lg / 2^(kLightOne - i + 1), or ll 2^(i - kLightOne - 1)
         for (uint32_t i = 0; i < kLightClasses; ++i) {
             const uint32_t a = i + qmax <= kLightOne ? nu
                                                      : units_in((i > kLightOne ? ll << (i - kLightOne - 1)
-                                                                               : ll >> (kLightOne - i + 1)) / 8);
+                                                                               : lg >> (kLightOne - i + 1)) / 8);
             d.lcls[i] = a > nh ? a - nh : 0u;
             if (i) d.lcls[i] = std::min(d.lcls[i], d.lcls[i - 1]);
         }

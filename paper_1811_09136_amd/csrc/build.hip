@@ -19,6 +19,8 @@ namespace {
 constexpr int SCAN_THREADS = 256;
 constexpr int SCAN_ITEMS = 16;
 constexpr int SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
+constexpr int NODE_ITEMS = 4;
+constexpr int NODE_TILE = SCAN_THREADS * NODE_ITEMS;  // nodes per workgroup of the slice scan
 constexpr int MEDIUM_MAX = 4096;  // segments sorted in LDS by one workgroup
 constexpr int WAVE_MAX = 1024;    // segments sorted in registers by one wavefront each
 constexpr int SMALL_MAX = 64;     // segments sorted in registers, several per wavefront
@@ -70,67 +72,113 @@ __device__ T block_reduce_sum256(T v) {
     return s;  // valid in thread 0
 }
 
-// ---------------------------------------------------------------- exclusive scan (u32) ----
-
-__global__ void __launch_bounds__(SCAN_THREADS) k_scan_reduce(const uint32_t* __restrict__ in, uint64_t N,
-                                                               uint32_t* __restrict__ part) {
-    const uint64_t base = (uint64_t)blockIdx.x * SCAN_TILE;
-    uint32_t s = 0;
-    for (int r = 0; r < SCAN_ITEMS; ++r) {
-        uint64_t i = base + (uint64_t)r * SCAN_THREADS + threadIdx.x;
-        if (i < N) s += in[i];
-    }
-    uint32_t t = block_reduce_sum256<uint32_t>(s);
-    if (threadIdx.x == 0) part[blockIdx.x] = t;
-}
-
-__global__ void __launch_bounds__(1024) k_scan_top(uint32_t* part, uint32_t nparts) {
-    __shared__ uint32_t wsum[16];
-    __shared__ uint32_t carry;
+__device__ uint32_t block_max256(uint32_t v) {  // valid in thread 0
+    __shared__ uint32_t red[SCAN_THREADS / 64];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
-    for (uint32_t base = 0; base < nparts; base += 1024) {
-        uint32_t i = base + threadIdx.x;
-        uint32_t v = i < nparts ? part[i] : 0;
-        uint32_t inc = wave_incl_scan(v);
-        if (lane == 63) wsum[wid] = inc;
-        __syncthreads();
-        uint32_t pre = 0, tot = 0;
-        for (int w = 0; w < 16; ++w) {
-            if (w < wid) pre += wsum[w];
-            tot += wsum[w];
-        }
-        uint32_t c = carry;
-        if (i < nparts) part[i] = c + pre + inc - v;
-        __syncthreads();
-        if (threadIdx.x == 0) carry = c + tot;
-        __syncthreads();
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        const uint32_t o = __shfl_xor(v, d, 64);
+        v = o > v ? o : v;
     }
+    if (lane == 0) red[wid] = v;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int w = 1; w < SCAN_THREADS / 64; ++w) v = red[w] > v ? red[w] : v;
+    __syncthreads();
+    return v;
 }
 
-// out[i] = sum of in[0..i), out[N] = total
-__global__ void __launch_bounds__(SCAN_THREADS) k_scan_down(const uint32_t* __restrict__ in, uint64_t N,
-                                                             const uint32_t* __restrict__ part,
-                                                             uint32_t* __restrict__ out) {
-    const uint64_t base = (uint64_t)blockIdx.x * SCAN_TILE + (uint64_t)threadIdx.x * SCAN_ITEMS;
+// ---------------------------------------------------------------- exclusive scan (u32) ----
+// One launch per scan.  A workgroup takes the next tile by a ticket, sums it, publishes the sum and
+// adds up the sums of the tiles before it (wavefront 0, 64 tiles at a look) until it meets one that
+// has published its inclusive sum.  It only ever waits for tiles whose tickets were drawn before its
+// own, so their workgroups are running and every wait ends.  A tile's word holds its state and its sum
+// together, so no other ordering is needed.  (The three launches of a reduce-then-scan cost a small
+// graph more than the work: a build of 2,000 nodes took seven scans, 21 of its 47 launches.)
+struct Look {
+    uint32_t* ticket;
+    unsigned long long* tile;  // state << 32 | sum; 0: nothing yet
+};
+constexpr unsigned long long kTileSum = 1ull << 32, kTileIncl = 2ull << 32;
+
+__device__ __forceinline__ uint32_t look_ticket(const Look& L) {
+    __shared__ uint32_t t;
+    __syncthreads();
+    if (threadIdx.x == 0) t = atomicAdd(L.ticket, 1u);
+    __syncthreads();
+    return t;
+}
+
+// the sum of all tiles before `t`, given this tile's sum (every thread of a 256-thread workgroup)
+__device__ uint32_t look_back(const Look& L, uint32_t t, uint32_t sum) {
+    __shared__ uint32_t before;
+    const int lane = threadIdx.x & 63;
+    if (threadIdx.x < 64) {
+        if (lane == 0 && t)
+            __hip_atomic_store(&L.tile[t], kTileSum | sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t acc = 0;
+        for (int64_t at = (int64_t)t - 1; at >= 0;) {
+            const int64_t i = at - lane;
+            const unsigned long long w =
+                i >= 0 ? __hip_atomic_load(&L.tile[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kTileIncl;
+            const unsigned long long incl = __ballot(w >= kTileIncl), none = __ballot(w < kTileSum);
+            const int first = incl ? __builtin_ctzll(incl) : 63;  // the lanes 0 .. first are added up
+            if (none & (~0ull >> (63 - first))) {
+                __builtin_amdgcn_s_sleep(1);
+                continue;
+            }
+            uint32_t v = lane <= first ? (uint32_t)w : 0u;
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+            acc += v;
+            if (incl) break;
+            at -= 64;
+        }
+        if (lane == 0) {
+            __hip_atomic_store(&L.tile[t], kTileIncl | (uint32_t)(acc + sum), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+            before = acc;
+        }
+    }
+    __syncthreads();
+    return before;
+}
+
+// out[i] = sum of in[0..i), out[N] = total (`in` and `out` 16-byte aligned)
+__global__ void __launch_bounds__(SCAN_THREADS) k_scan(const uint32_t* __restrict__ in, uint64_t N,
+                                                        uint32_t* __restrict__ out, Look L) {
+    const uint32_t t = look_ticket(L);
+    const uint64_t base = (uint64_t)t * SCAN_TILE + (uint64_t)threadIdx.x * SCAN_ITEMS;
     uint32_t v[SCAN_ITEMS];
     uint32_t s = 0;
+    const bool full = base + SCAN_ITEMS <= N;
+    if (full) {
 #pragma unroll
-    for (int r = 0; r < SCAN_ITEMS; ++r) {
-        uint64_t i = base + r;
-        v[r] = i < N ? in[i] : 0;
-        s += v[r];
+        for (int r = 0; r < SCAN_ITEMS; r += 4) *(uint4*)&v[r] = *(const uint4*)(in + base + r);
+    } else {
+#pragma unroll
+        for (int r = 0; r < SCAN_ITEMS; ++r) v[r] = base + r < N ? in[base + r] : 0;
     }
+#pragma unroll
+    for (int r = 0; r < SCAN_ITEMS; ++r) s += v[r];
     uint32_t total;
-    uint32_t pre = block_excl_scan256(s, total) + part[blockIdx.x];
+    uint32_t pre = block_excl_scan256(s, total);
+    pre += look_back(L, t, total);
 #pragma unroll
     for (int r = 0; r < SCAN_ITEMS; ++r) {
-        uint64_t i = base + r;
-        if (i < N) out[i] = pre;
-        pre += v[r];
+        const uint32_t c = v[r];
+        v[r] = pre;
+        pre += c;
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == SCAN_THREADS - 1) out[N] = pre;
+    if (full) {
+#pragma unroll
+        for (int r = 0; r < SCAN_ITEMS; r += 4) *(uint4*)(out + base + r) = *(const uint4*)&v[r];
+    } else {
+#pragma unroll
+        for (int r = 0; r < SCAN_ITEMS; ++r)
+            if (base + r < N) out[base + r] = v[r];
+    }
+    if (t == gridDim.x - 1 && threadIdx.x == SCAN_THREADS - 1) out[N] = pre;
 }
 
 // ---------------------------------------------------------------- build kernels ----------
@@ -139,6 +187,47 @@ __global__ void k_fill_u32(uint32_t* p, uint64_t count, uint32_t v) {
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
          i += (uint64_t)gridDim.x * blockDim.x)
         p[i] = v;
+}
+
+// the counters a build starts from, cleared in one launch
+struct Clear {
+    uint32_t* p[5];
+    uint64_t words[5];
+};
+__global__ void k_clear(Clear C) {
+    const uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (uint64_t)gridDim.x * blockDim.x;
+#pragma unroll
+    for (int r = 0; r < 5; ++r)
+        for (uint64_t i = i0; i < C.words[r]; i += stride) C.p[r][i] = 0u;
+}
+
+// Degrees of a small graph (at most DEG_DIRECT nodes): each workgroup counts its edges' endpoints in
+// LDS, all nodes at once, and adds its counts; the same checks as k_deg_hist.  (200k edges, 10k nodes:
+// one launch in place of a partition's six.)
+constexpr uint32_t DEG_DIRECT = 16384;
+__global__ void __launch_bounds__(1024) k_deg_direct(const uint2* __restrict__ edges, uint64_t E, uint32_t n,
+                                                     uint64_t per_block, uint32_t* __restrict__ deg, BuildStats* st) {
+    __shared__ uint32_t cnt[DEG_DIRECT];
+    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) cnt[i] = 0;
+    __syncthreads();
+    const uint64_t e0 = (uint64_t)blockIdx.x * per_block;
+    const uint64_t e1 = (e0 + per_block) < E ? (e0 + per_block) : E;
+    uint32_t bad = 0;
+    for (uint64_t t = e0 + threadIdx.x; t < e1; t += blockDim.x) {
+        const uint2 e = edges[t];
+        if (e.x >= n || e.y >= n) {
+            bad |= RF_RANGE;
+        } else if (e.x == e.y) {
+            bad |= RF_SELFLOOP;
+        } else {
+            atomicAdd(&cnt[e.x], 1u);
+            atomicAdd(&cnt[e.y], 1u);
+        }
+    }
+    if (bad) atomicOr(&st->flags, bad);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x)
+        if (cnt[i]) atomicAdd(&deg[i], cnt[i]);
 }
 
 // ---- degrees without global atomics: endpoints are partitioned into buckets of 2^shift
@@ -318,22 +407,6 @@ __global__ void __launch_bounds__(1024) k_orient_hist(const uint2* __restrict__ 
     for (uint32_t b = threadIdx.x; b < NB; b += blockDim.x) bhist[(uint64_t)b * gridDim.x + blockIdx.x] = h[b];
 }
 
-// the oriented entries (a, b, t) in bucket order of a (order within a bucket is free)
-__global__ void __launch_bounds__(1024) k_orient_part(const uint2* __restrict__ ab, uint64_t E, uint32_t shift,
-                                                      uint32_t NB, uint64_t per_block,
-                                                      const uint32_t* __restrict__ boff, OEntry* __restrict__ opart) {
-    __shared__ uint32_t base[DEG_BUCKETS];
-    for (uint32_t b = threadIdx.x; b < NB; b += blockDim.x) base[b] = boff[(uint64_t)b * gridDim.x + blockIdx.x];
-    __syncthreads();
-    const uint64_t e0 = (uint64_t)blockIdx.x * per_block;
-    const uint64_t e1 = (e0 + per_block) < E ? (e0 + per_block) : E;
-    for (uint64_t t = e0 + threadIdx.x; t < e1; t += blockDim.x) {
-        const uint2 e = ab[t];
-        if (e.x == NO_EDGE) continue;
-        opart[atomicAdd(&base[e.x >> shift], 1u)] = OEntry{e.x, e.y, (uint32_t)t};
-    }
-}
-
 // out-degrees: workgroups take fixed slices of the partition and count each bucket's part of
 // the slice in LDS, one atomic per distinct node (`dout` zero on entry)
 __global__ void __launch_bounds__(1024) k_out_count(const OEntry* __restrict__ opart,
@@ -376,35 +449,71 @@ __global__ void __launch_bounds__(1024) k_out_count(const OEntry* __restrict__ o
 // each slice (its segment start plus its entries in the bucket's earlier slices); a slice then
 // places its entries with LDS cursors from those bases.  Needs a bucket span of at most DEG_SUB
 // ids (n <= 2^25).
-// (R-MAT scale 24 build: 45.6-46.0 ms at 32768 entries, 45.9 at 65536, 46.9 at 16384, 48.4 at
-// 8192: fewer slices per bucket write fewer per-slice counts and interleave less in each
-// node's segment)
-constexpr uint32_t SLICE_ENTRIES = 32768;
+// At most SLICE_MAX entries a slice (R-MAT scale 24 build: 45.6-46.0 ms at 32768 entries, 45.9 at
+// 65536, 46.9 at 16384, 48.4 at 8192: fewer slices per bucket write fewer per-slice counts and
+// interleave less in each node's segment); fewer where E would leave compute units without a slice
+// (200k edges: the two placements 48 and 50 us with ten slices of 32768, 25 and 7 with slices of 2048).
+constexpr uint32_t SLICE_MAX = 32768, SLICE_MIN = 2048;
+__host__ __device__ inline uint32_t slice_entries(uint64_t E) {
+    uint32_t s = SLICE_MIN;
+    while (s < SLICE_MAX && (uint64_t)s * 256 < E) s <<= 1;
+    return s;
+}
 
-// slice_off[b] = first slice of bucket b (slice_off[NB] = the number of slices); one workgroup
-__global__ void __launch_bounds__(1024) k_slice_plan(const uint32_t* __restrict__ boff, uint32_t nblk, uint32_t NB,
-                                                     uint32_t* __restrict__ slice_off) {
-    __shared__ uint32_t cnt[DEG_BUCKETS];
-    const uint32_t total = boff[(uint64_t)NB * nblk];
-    for (uint32_t b = threadIdx.x; b < NB; b += blockDim.x) {
-        const uint32_t lo = boff[(uint64_t)b * nblk], hi = (b + 1 < NB) ? boff[(uint64_t)(b + 1) * nblk] : total;
-        cnt[b] = (hi - lo + SLICE_ENTRIES - 1) / SLICE_ENTRIES;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t run = 0;
-        for (uint32_t b = 0; b < NB; ++b) {
-            slice_off[b] = run;
-            run += cnt[b];
+// slice_off[b] = first slice of bucket b (slice_off[NB] = the number of slices): one workgroup of 1024
+// threads, in the partition's launch; `lds` holds DEG_BUCKETS words
+__device__ void slice_plan(const uint32_t* __restrict__ boff, uint32_t nblk, uint32_t NB,
+                           uint32_t* __restrict__ slice_off, uint32_t slice, uint32_t* lds) {
+    constexpr uint32_t kPer = DEG_BUCKETS / 1024;
+    const uint32_t total = boff[(uint64_t)NB * nblk], lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    uint32_t c[kPer], s = 0;
+#pragma unroll
+    for (uint32_t r = 0; r < kPer; ++r) {
+        const uint32_t b = threadIdx.x * kPer + r;
+        c[r] = 0;
+        if (b < NB) {
+            const uint32_t lo = boff[(uint64_t)b * nblk], hi = (b + 1 < NB) ? boff[(uint64_t)(b + 1) * nblk] : total;
+            c[r] = (hi - lo + slice - 1) / slice;
         }
-        slice_off[NB] = run;
+        s += c[r];
+    }
+    const uint32_t inc = wave_incl_scan(s);
+    if (lane == 63) lds[wid] = inc;
+    __syncthreads();
+    uint32_t run = inc - s;
+    for (uint32_t w = 0; w < wid; ++w) run += lds[w];
+#pragma unroll
+    for (uint32_t r = 0; r < kPer; ++r) {
+        const uint32_t b = threadIdx.x * kPer + r;
+        if (b <= NB) slice_off[b] = run;
+        run += c[r];
+    }
+    if (NB == DEG_BUCKETS && threadIdx.x == 1023) slice_off[NB] = run;
+    __syncthreads();
+}
+
+// the oriented entries (a, b, t) in bucket order of a (order within a bucket is free)
+__global__ void __launch_bounds__(1024) k_orient_part(const uint2* __restrict__ ab, uint64_t E, uint32_t shift,
+                                                      uint32_t NB, uint64_t per_block,
+                                                      const uint32_t* __restrict__ boff, OEntry* __restrict__ opart,
+                                                      uint32_t* __restrict__ slice_off, uint32_t slice) {
+    __shared__ uint32_t base[DEG_BUCKETS];
+    if (slice_off && blockIdx.x == 0) slice_plan(boff, gridDim.x, NB, slice_off, slice, base);
+    for (uint32_t b = threadIdx.x; b < NB; b += blockDim.x) base[b] = boff[(uint64_t)b * gridDim.x + blockIdx.x];
+    __syncthreads();
+    const uint64_t e0 = (uint64_t)blockIdx.x * per_block;
+    const uint64_t e1 = (e0 + per_block) < E ? (e0 + per_block) : E;
+    for (uint64_t t = e0 + threadIdx.x; t < e1; t += blockDim.x) {
+        const uint2 e = ab[t];
+        if (e.x == NO_EDGE) continue;
+        opart[atomicAdd(&base[e.x >> shift], 1u)] = OEntry{e.x, e.y, (uint32_t)t};
     }
 }
 
 // the slice of workgroup s: its bucket b and entry range [lo, hi); false past the last slice
 __device__ __forceinline__ bool slice_of(uint32_t s, const uint32_t* __restrict__ slice_off,
-                                         const uint32_t* __restrict__ boff, uint32_t nblk, uint32_t NB, uint32_t& b,
-                                         uint64_t& lo, uint64_t& hi) {
+                                         const uint32_t* __restrict__ boff, uint32_t nblk, uint32_t NB, uint32_t slice,
+                                         uint32_t& b, uint64_t& lo, uint64_t& hi) {
     if (s >= slice_off[NB]) return false;
     uint32_t l = 0, h = NB;  // last bucket with slice_off[b] <= s
     while (h - l > 1) {
@@ -415,8 +524,8 @@ __device__ __forceinline__ bool slice_of(uint32_t s, const uint32_t* __restrict_
     b = l;
     const uint32_t total = boff[(uint64_t)NB * nblk];
     const uint64_t b0 = boff[(uint64_t)b * nblk], b1 = (b + 1 < NB) ? boff[(uint64_t)(b + 1) * nblk] : total;
-    lo = b0 + (uint64_t)(s - slice_off[b]) * SLICE_ENTRIES;
-    hi = (lo + SLICE_ENTRIES) < b1 ? (lo + SLICE_ENTRIES) : b1;
+    lo = b0 + (uint64_t)(s - slice_off[b]) * slice;
+    hi = (lo + slice) < b1 ? (lo + slice) : b1;
     return true;
 }
 
@@ -425,11 +534,11 @@ template <typename T>
 __global__ void __launch_bounds__(1024) k_slice_count(const T* __restrict__ opart,
                                                       const uint32_t* __restrict__ boff, uint32_t nblk, uint32_t NB,
                                                       uint32_t shift, const uint32_t* __restrict__ slice_off,
-                                                      uint32_t* __restrict__ scount) {
+                                                      uint32_t slice, uint32_t* __restrict__ scount) {
     __shared__ uint32_t cnt[DEG_SUB];
     uint32_t b;
     uint64_t lo, hi;
-    if (!slice_of(blockIdx.x, slice_off, boff, nblk, NB, b, lo, hi)) return;
+    if (!slice_of(blockIdx.x, slice_off, boff, nblk, NB, slice, b, lo, hi)) return;
     const uint32_t span = 1u << shift, v0 = b << shift;
     for (uint32_t i = threadIdx.x; i < span; i += blockDim.x) cnt[i] = 0;
     __syncthreads();
@@ -439,28 +548,118 @@ __global__ void __launch_bounds__(1024) k_slice_count(const T* __restrict__ opar
     for (uint32_t i = threadIdx.x; i < span; i += blockDim.x) out[i] = cnt[i];
 }
 
-// dout[v] = the entries of v over its bucket's slices
-__global__ void k_slice_dout(const uint32_t* __restrict__ scount, const uint32_t* __restrict__ slice_off,
-                             uint32_t shift, uint32_t n, uint32_t* __restrict__ dout) {
-    for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
-        const uint32_t b = v >> shift, i = v - (b << shift), span = 1u << shift;
-        uint32_t d = 0;
-        for (uint32_t s = slice_off[b]; s < slice_off[b + 1]; ++s) d += scount[(uint64_t)s * span + i];
-        dout[v] = d;
-    }
+// A unit's order key and the segment classes of the sorts (below), per node.  `medium` lists the
+// wavefront class from its front and the workgroup class from its back.
+struct Classes {
+    uint32_t *medium, *large;
+    BuildStats* st;
+};
+__device__ __forceinline__ uint32_t size_class(uint32_t d) {  // 0, 1, 2: medium, large, wave; 3: the rest
+    return d <= (uint32_t)SMALL_MAX ? 3u : (d <= (uint32_t)WAVE_MAX ? 2u : (d <= (uint32_t)MEDIUM_MAX ? 0u : 1u));
 }
 
-// scount[s][i] <- the position of node v's first entry of slice s in v's segment
-__global__ void k_slice_base(uint32_t* __restrict__ scount, const uint32_t* __restrict__ slice_off,
-                             uint32_t shift, uint32_t n, const uint32_t* __restrict__ off) {
-    for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
-        const uint32_t b = v >> shift, i = v - (b << shift), span = 1u << shift;
-        uint32_t run = off[v];
-        for (uint32_t s = slice_off[b]; s < slice_off[b + 1]; ++s) {
-            uint32_t* c = scount + (uint64_t)s * span + i;
-            const uint32_t k = *c;
-            *c = run;
-            run += k;
+// off[v] from the slices' counts, in one pass over the nodes: v's entries over its bucket's slices
+// (-> dout, if wanted), their exclusive scan (-> off, off[n] = total), and scount[s][v] <- the position
+// of v's first entry of slice s in v's segment.  CLASSIFY: also the segments' size classes and the
+// oriented graph's statistics.  A workgroup takes NODE_TILE nodes, four consecutive ones per thread.
+template <bool CLASSIFY>
+__global__ void __launch_bounds__(SCAN_THREADS) k_slice_scan(uint32_t* __restrict__ scount,
+                                                             const uint32_t* __restrict__ slice_off, uint32_t shift,
+                                                             uint32_t n, uint32_t* __restrict__ dout,
+                                                             uint32_t* __restrict__ off, Look L, Classes C) {
+    static_assert(NODE_ITEMS == 4, "a 16-byte load per slice");
+    // slices read at a time: the bucket of the top-degree nodes has many (1M nodes and 20M edges: 44),
+    // and read one by one they set the launch's length
+    constexpr uint32_t kBatch = 8;
+    const uint32_t t = look_ticket(L);
+    const uint64_t v0 = (uint64_t)t * NODE_TILE + (uint64_t)threadIdx.x * NODE_ITEMS, span = 1ull << shift;
+    uint32_t d[4] = {0u, 0u, 0u, 0u};
+    uint32_t s0 = 0, s1 = 0;
+    uint64_t i = 0;
+    if (v0 < n) {  // (the four nodes share a bucket: spans are multiples of four)
+        const uint32_t b = (uint32_t)(v0 >> shift);
+        i = v0 - ((uint64_t)b << shift);
+        s0 = slice_off[b];
+        s1 = slice_off[b + 1];
+        for (uint32_t s = s0; s < s1; s += kBatch) {
+            uint4 c[kBatch];
+#pragma unroll
+            for (uint32_t r = 0; r < kBatch; ++r)
+                c[r] = s + r < s1 ? *(const uint4*)(scount + (s + r) * span + i) : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+            for (uint32_t r = 0; r < kBatch; ++r) {
+                d[0] += c[r].x;
+                d[1] += c[r].y;
+                d[2] += c[r].z;
+                d[3] += c[r].w;
+            }
+        }
+    }
+    uint32_t total;
+    uint32_t pre = block_excl_scan256(d[0] + d[1] + d[2] + d[3], total);
+    pre += look_back(L, t, total);
+    uint32_t run[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        run[r] = pre;
+        if (v0 + r < n) {
+            off[v0 + r] = pre;
+            if (dout) dout[v0 + r] = d[r];
+        }
+        pre += d[r];
+    }
+    if (t == gridDim.x - 1 && threadIdx.x == SCAN_THREADS - 1) off[n] = pre;
+    for (uint32_t s = s0; s < s1; s += kBatch) {
+        uint4 c[kBatch];
+#pragma unroll
+        for (uint32_t r = 0; r < kBatch; ++r)
+            if (s + r < s1) c[r] = *(const uint4*)(scount + (s + r) * span + i);
+#pragma unroll
+        for (uint32_t r = 0; r < kBatch; ++r) {
+            if (s + r >= s1) break;
+            *(uint4*)(scount + (s + r) * span + i) = make_uint4(run[0], run[1], run[2], run[3]);
+            run[0] += c[r].x;
+            run[1] += c[r].y;
+            run[2] += c[r].z;
+            run[3] += c[r].w;
+        }
+    }
+    if (CLASSIFY) {
+        __shared__ uint32_t cnt[3], base[3];
+        if (threadIdx.x < 3) cnt[threadIdx.x] = 0;
+        __syncthreads();
+        unsigned long long sq = 0;
+        uint32_t mx = 0, napex = 0, at[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            sq += (unsigned long long)d[r] * d[r];
+            mx = d[r] > mx ? d[r] : mx;
+            napex += d[r] >= 2 ? 1u : 0u;
+            const uint32_t k = size_class(d[r]);
+            at[r] = k < 3 ? atomicAdd(&cnt[k], 1u) : 0u;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            base[0] = cnt[0] ? atomicAdd(&C.st->n_medium, cnt[0]) : 0;
+            base[1] = cnt[1] ? atomicAdd(&C.st->n_large, cnt[1]) : 0;
+            base[2] = cnt[2] ? atomicAdd(&C.st->n_wave, cnt[2]) : 0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t k = size_class(d[r]), v = (uint32_t)(v0 + r);
+            if (k == 0) C.medium[n - 1 - (base[0] + at[r])] = v;
+            else if (k == 1) C.large[base[1] + at[r]] = v;
+            else if (k == 2) C.medium[base[2] + at[r]] = v;
+        }
+        const unsigned long long s = block_reduce_sum256<unsigned long long>(sq);
+        const uint32_t na = block_reduce_sum256<uint32_t>(napex);
+        mx = block_max256(mx);
+        if (threadIdx.x == 0) {
+            StatPart& P = C.st->part[t % kStatParts];
+            if (mx) atomicMax(&P.max_out, mx);
+            if (s) atomicAdd(&P.sum_out_sq, s);
+            if (na) atomicAdd(&P.num_apex, na);
         }
     }
 }
@@ -472,14 +671,14 @@ constexpr uint32_t REV_BIT = REPT_REV_BIT;
 __global__ void __launch_bounds__(1024) k_slice_place(const OEntry* __restrict__ opart,
                                                       const uint32_t* __restrict__ boff, uint32_t nblk, uint32_t NB,
                                                       uint32_t shift, const uint32_t* __restrict__ slice_off,
-                                                      const uint32_t* __restrict__ sbase,
+                                                      uint32_t slice, const uint32_t* __restrict__ sbase,
                                                       const uint32_t* __restrict__ dout,
                                                       unsigned long long* __restrict__ packed,
                                                       uint32_t* __restrict__ rcnt, BuildStats* st) {
     __shared__ uint32_t cur[DEG_SUB];
     uint32_t b;
     uint64_t lo, hi;
-    if (!slice_of(blockIdx.x, slice_off, boff, nblk, NB, b, lo, hi)) return;
+    if (!slice_of(blockIdx.x, slice_off, boff, nblk, NB, slice, b, lo, hi)) return;
     const uint32_t span = 1u << shift, v0 = b << shift;
     const uint32_t* base = sbase + (uint64_t)blockIdx.x * span;
     for (uint32_t i = threadIdx.x; i < span; i += blockDim.x) cur[i] = base[i];
@@ -513,9 +712,14 @@ __global__ void __launch_bounds__(1024) k_slice_place(const OEntry* __restrict__
             if (rev && rcnt) atomicAdd(&rcnt[(uint64_t)e[u].b * REV_SHARDS + (e[u].a % REV_SHARDS)], 1u);
         }
     }
+    __shared__ unsigned long long wsum;
+    if (threadIdx.x == 0) wsum = 0;
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) work += __shfl_xor(work, d, 64);
-    if ((threadIdx.x & 63) == 0 && work) atomicAdd(&st->work, work);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0 && work) atomicAdd(&wsum, work);
+    __syncthreads();
+    if (threadIdx.x == 0 && wsum) atomicAdd(&st->part[blockIdx.x % kStatParts].work, wsum);
 }
 
 // ---- reverse lists by a bucketed transpose (bucket spans of at most DEG_SUB ids): after the
@@ -545,8 +749,10 @@ __global__ void __launch_bounds__(1024) k_rev_hist(const uint32_t* __restrict__ 
 __global__ void __launch_bounds__(1024) k_rev_part(const uint32_t* __restrict__ rsrc, const uint32_t* __restrict__ nbr,
                                                    const uint32_t* __restrict__ tim, const uint32_t* __restrict__ off,
                                                    uint32_t n, uint32_t shift, uint32_t NB, uint64_t per_block,
-                                                   const uint32_t* __restrict__ boff, uint4* __restrict__ rpart) {
+                                                   const uint32_t* __restrict__ boff, uint4* __restrict__ rpart,
+                                                   uint32_t* __restrict__ slice_off, uint32_t slice) {
     __shared__ uint32_t base[DEG_BUCKETS];
+    if (blockIdx.x == 0) slice_plan(boff, gridDim.x, NB, slice_off, slice, base);
     for (uint32_t b = threadIdx.x; b < NB; b += blockDim.x) base[b] = boff[(uint64_t)b * gridDim.x + blockIdx.x];
     __syncthreads();
     const uint64_t total = off[n];
@@ -564,13 +770,13 @@ __global__ void __launch_bounds__(1024) k_rev_part(const uint32_t* __restrict__ 
 // out(a)) and the pair's adjacency position
 __global__ void __launch_bounds__(1024) k_rev_place(const uint4* __restrict__ rpart, const uint32_t* __restrict__ boff,
                                                     uint32_t nblk, uint32_t NB, uint32_t shift,
-                                                    const uint32_t* __restrict__ slice_off,
+                                                    const uint32_t* __restrict__ slice_off, uint32_t slice,
                                                     const uint32_t* __restrict__ sbase, const uint32_t* __restrict__ off,
                                                     uint4* __restrict__ rrec, uint32_t* __restrict__ rpos) {
     __shared__ uint32_t cur[DEG_SUB];
     uint32_t b;
     uint64_t lo, hi;
-    if (!slice_of(blockIdx.x, slice_off, boff, nblk, NB, b, lo, hi)) return;
+    if (!slice_of(blockIdx.x, slice_off, boff, nblk, NB, slice, b, lo, hi)) return;
     const uint32_t span = 1u << shift, v0 = b << shift;
     const uint32_t* base = sbase + (uint64_t)blockIdx.x * span;
     for (uint32_t i = threadIdx.x; i < span; i += blockDim.x) cur[i] = base[i];
@@ -641,7 +847,7 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scatter(const uint2* __restric
         }
     }
     unsigned long long s = block_reduce_sum256<unsigned long long>(work);
-    if (threadIdx.x == 0 && s) atomicAdd(&st->work, s);
+    if (threadIdx.x == 0 && s) atomicAdd(&st->part[blockIdx.x % kStatParts].work, s);
 }
 
 // Reverse lists.  The counting pass finds a triangle from its lowest-ranked oriented pair
@@ -674,8 +880,6 @@ __device__ __forceinline__ void node_range(uint32_t n, uint32_t& a0, uint32_t& a
     if (a0 > n) a0 = n;
 }
 
-// classify segments by size (sort path: `medium` lists the wavefront class from its front and the
-// workgroup class from its back), and the statistics of the oriented graph
 // unit order key of node a (REPT_REV_SHIFT), at most n - 1; units are ordered by it, descending,
 // and the counting pass gives a workgroup to the units whose key exceeds its wavefront cap
 __device__ __forceinline__ uint32_t unit_key(const uint32_t* __restrict__ off, const uint32_t* __restrict__ roff,
@@ -685,6 +889,8 @@ __device__ __forceinline__ uint32_t unit_key(const uint32_t* __restrict__ off, c
     return k < n - 1 ? k : n - 1;
 }
 
+// the segments' size classes and the oriented graph's statistics (wide buckets: k_slice_scan does it
+// otherwise)
 __global__ void __launch_bounds__(SCAN_THREADS) k_classify(const uint32_t* __restrict__ off, uint32_t n,
                                                            uint32_t* medium, uint32_t* large, BuildStats* st) {
     __shared__ uint32_t cnt[3], base[3];
@@ -699,9 +905,7 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_classify(const uint32_t* __res
         sq += (unsigned long long)d * d;
         mx = d > mx ? d : mx;
         if (d >= 2) ++napex;
-        if (d > WAVE_MAX && d <= MEDIUM_MAX) atomicAdd(&cnt[0], 1u);
-        if (d > MEDIUM_MAX) atomicAdd(&cnt[1], 1u);
-        if (d > SMALL_MAX && d <= WAVE_MAX) atomicAdd(&cnt[2], 1u);
+        if (size_class(d) < 3) atomicAdd(&cnt[size_class(d)], 1u);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -712,21 +916,19 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_classify(const uint32_t* __res
     __syncthreads();
     for (uint32_t a = a0 + threadIdx.x; a < a1; a += blockDim.x) {
         const uint32_t d = off[a + 1] - off[a];
-        if (d > WAVE_MAX && d <= MEDIUM_MAX) medium[n - 1 - atomicAdd(&base[0], 1u)] = a;
-        if (d > MEDIUM_MAX) large[atomicAdd(&base[1], 1u)] = a;
-        if (d > SMALL_MAX && d <= WAVE_MAX) medium[atomicAdd(&base[2], 1u)] = a;
+        const uint32_t k = size_class(d);
+        if (k == 0) medium[n - 1 - atomicAdd(&base[0], 1u)] = a;
+        else if (k == 1) large[atomicAdd(&base[1], 1u)] = a;
+        else if (k == 2) medium[atomicAdd(&base[2], 1u)] = a;
     }
     unsigned long long s = block_reduce_sum256<unsigned long long>(sq);
     uint32_t na = block_reduce_sum256<uint32_t>(napex);
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        uint32_t o = __shfl_xor(mx, d, 64);
-        mx = o > mx ? o : mx;
-    }
-    if ((threadIdx.x & 63) == 0 && mx) atomicMax(&st->max_out, mx);
+    mx = block_max256(mx);
     if (threadIdx.x == 0) {
-        if (s) atomicAdd(&st->sum_out_sq, s);
-        if (na) atomicAdd(&st->num_apex, na);
+        StatPart& P = st->part[blockIdx.x % kStatParts];
+        if (mx) atomicMax(&P.max_out, mx);
+        if (s) atomicAdd(&P.sum_out_sq, s);
+        if (na) atomicAdd(&P.num_apex, na);
     }
 }
 
@@ -855,8 +1057,9 @@ __device__ __forceinline__ unsigned long long group_sort(unsigned long long v, u
     return v;
 }
 
-// Segments of 1..64 entries.  A wavefront takes 64 consecutive nodes at a time (one coalesced
-// load of their offsets) and sorts their segments in aligned lane groups of 8, 16, 32 or 64
+// Segments of 1..64 entries.  A wavefront takes `per` (at most 64) consecutive nodes at a time (one
+// coalesced load of their offsets; a small graph's nodes are spread over more wavefronts: 10k nodes
+// and 200k edges, 99 us at 64, 20 at 4) and sorts their segments in aligned lane groups of 8, 16, 32 or 64
 // lanes (the smallest that holds the segment), 64 / G segments per pass, so a short segment
 // costs a short network and shares it with others.
 template <int G>
@@ -884,17 +1087,18 @@ __device__ __forceinline__ void sort_class(bool in, uint32_t s, uint32_t d, uint
     }
 }
 
-__global__ void __launch_bounds__(256) k_sort_small(const uint32_t* __restrict__ off, uint32_t n,
+__global__ void __launch_bounds__(256) k_sort_small(const uint32_t* __restrict__ off, uint32_t n, uint32_t per,
                                                     const unsigned long long* __restrict__ packed,
                                                     uint32_t* __restrict__ nbr, uint32_t* __restrict__ tim,
                                                     RevOut R, BuildStats* st) {
     const int lane = threadIdx.x & 63;
     const uint64_t waves = (uint64_t)gridDim.x * (blockDim.x >> 6);
     uint32_t dup = 0;
-    for (uint64_t a0 = ((uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 64; a0 < n; a0 += waves * 64) {
+    for (uint64_t a0 = ((uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * per; a0 < n;
+         a0 += waves * per) {
         const uint64_t a = a0 + lane;
         uint32_t s = 0, d = 0;
-        if (a < n) {
+        if ((uint32_t)lane < per && a < n) {
             s = off[a];
             d = off[a + 1] - s;
         }
@@ -982,13 +1186,11 @@ __global__ void __launch_bounds__(256) k_sort_wave(const uint32_t* __restrict__ 
 
 // segments of 1025..4096 entries: one workgroup, bitonic sort in LDS (their nodes are listed
 // from the back of `list`, which holds n entries)
-__global__ void __launch_bounds__(512) k_sort_medium(const uint32_t* __restrict__ off, const uint32_t* __restrict__ list,
-                                                     uint32_t n, const unsigned long long* __restrict__ packed,
-                                                     uint32_t* __restrict__ nbr, uint32_t* __restrict__ tim,
-                                                     RevOut R, BuildStats* st) {
-    __shared__ unsigned long long buf[MEDIUM_MAX];
+__device__ void sort_medium(const uint32_t* __restrict__ off, const uint32_t* __restrict__ list, uint32_t n,
+                            const unsigned long long* packed, uint32_t* __restrict__ nbr, uint32_t* __restrict__ tim,
+                            const RevOut& R, BuildStats* st, uint32_t block, uint32_t blocks, unsigned long long* buf) {
     const uint32_t cnt = st->n_medium;
-    for (uint32_t q = blockIdx.x; q < cnt; q += gridDim.x) {
+    for (uint32_t q = block; q < cnt; q += blocks) {
         const uint32_t a = list[n - 1 - q];
         const uint32_t s = off[a], d = off[a + 1] - s;
         uint32_t P = 128;
@@ -1022,17 +1224,23 @@ __global__ void __launch_bounds__(512) k_sort_medium(const uint32_t* __restrict_
     }
 }
 
+// orders a wavefront's own LDS and memory accesses (of all its lanes)
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+}
+
 // segments above 4096 entries: one wavefront, stable LSD radix sort (8-bit digits of the
 // neighbour id) ping-ponging between `packed` and `alt` over the segment's own range
-__global__ void __launch_bounds__(64) k_sort_large(const uint32_t* __restrict__ off, const uint32_t* __restrict__ list,
-                                                   unsigned long long* packed, unsigned long long* alt,
-                                                   uint32_t id_bits, uint32_t* __restrict__ nbr,
-                                                   uint32_t* __restrict__ tim, RevOut R, BuildStats* st) {
-    __shared__ uint32_t base[256];
+__device__ void sort_large(const uint32_t* __restrict__ off, const uint32_t* __restrict__ list,
+                           unsigned long long* packed, unsigned long long* alt, uint32_t id_bits,
+                           uint32_t* __restrict__ nbr, uint32_t* __restrict__ tim, const RevOut& R, BuildStats* st,
+                           uint32_t block, uint32_t blocks, uint32_t* base) {
     const int lane = threadIdx.x;
     const uint32_t cnt = st->n_large;
     const uint32_t passes = (id_bits + 7) / 8;
-    for (uint32_t q = blockIdx.x; q < cnt; q += gridDim.x) {
+    for (uint32_t q = block; q < cnt; q += blocks) {
         const uint32_t a = list[q];
         const uint32_t s = off[a], d = off[a + 1] - s;
         unsigned long long* src = packed + s;
@@ -1040,9 +1248,9 @@ __global__ void __launch_bounds__(64) k_sort_large(const uint32_t* __restrict__ 
         for (uint32_t pass = 0; pass < passes; ++pass) {
             const uint32_t shift = 32 + 8 * pass;
             for (int b = lane; b < 256; b += 64) base[b] = 0;
-            __syncthreads();
+            wave_fence();
             for (uint32_t i = lane; i < d; i += 64) atomicAdd(&base[(uint32_t)(src[i] >> shift) & 255u], 1u);
-            __syncthreads();
+            wave_fence();
             if (lane == 0) {
                 uint32_t run = 0;
                 for (int b = 0; b < 256; ++b) {
@@ -1051,7 +1259,7 @@ __global__ void __launch_bounds__(64) k_sort_large(const uint32_t* __restrict__ 
                     run += c;
                 }
             }
-            __syncthreads();
+            wave_fence();
             for (uint32_t c0 = 0; c0 < d; c0 += 64) {
                 const uint32_t i = c0 + lane;
                 const bool valid = i < d;
@@ -1065,13 +1273,13 @@ __global__ void __launch_bounds__(64) k_sort_large(const uint32_t* __restrict__ 
                 const unsigned long long lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
                 uint32_t rank = __popcll(peers & lt);
                 uint32_t pos = valid ? base[dig] + rank : 0;
-                __syncthreads();
+                wave_fence();
                 if (valid) {
                     dst[pos] = v;
                     int last = 63 - __clzll(peers);
                     if (lane == last) base[dig] += __popcll(peers);
                 }
-                __syncthreads();
+                wave_fence();
             }
             unsigned long long* tmp = src;
             src = dst;
@@ -1084,8 +1292,21 @@ __global__ void __launch_bounds__(64) k_sort_large(const uint32_t* __restrict__ 
             emit_sorted(v, i, a, s, d, nbr, tim, R);
         }
         if (dup) atomicOr(&st->flags, RF_DUP);
-        __syncthreads();
+        wave_fence();
     }
+}
+
+// the segments above 1024 entries: a workgroup takes the 1025..4096 ones, then its first wavefront the
+// larger ones (one launch: most graphs have neither)
+__global__ void __launch_bounds__(512) k_sort_rest(const uint32_t* __restrict__ off, const uint32_t* __restrict__ medium,
+                                                   const uint32_t* __restrict__ large, uint32_t n,
+                                                   unsigned long long* packed, unsigned long long* alt,
+                                                   uint32_t id_bits, uint32_t* __restrict__ nbr,
+                                                   uint32_t* __restrict__ tim, RevOut R, BuildStats* st) {
+    __shared__ unsigned long long buf[MEDIUM_MAX];
+    sort_medium(off, medium, n, packed, nbr, tim, R, st, blockIdx.x, gridDim.x, buf);
+    if (threadIdx.x < 64)
+        sort_large(off, large, packed, alt, id_bits, nbr, tim, R, st, blockIdx.x, gridDim.x, (uint32_t*)buf);
 }
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -1094,7 +1315,7 @@ struct Layout {
     size_t ctrl, off, nbr, tim, apex, roff, rrec, rpos, total;
 };
 struct ScratchLayout {
-    size_t stats, deg, dout, cursor, ahist, aoff, part, packed, alt, opart, slice_off, scount, medium, large, bhist,
+    size_t stats, deg, dout, cursor, ahist, aoff, look, packed, alt, opart, slice_off, scount, medium, large, bhist,
         bscan, scnt, sofs, total;
 };
 
@@ -1140,6 +1361,25 @@ Layout persistent_layout(uint32_t n, uint64_t E) {
     return L;
 }
 
+// Where each scan of a build has its ticket and tile words: at[k], 64-bit words, the ticket first.
+enum { LOOK_DEG1, LOOK_DEG2, LOOK_ORIENT, LOOK_OFF, LOOK_REV, LOOK_ROFF, LOOK_APEX, LOOK_SHARD, LOOKS };
+struct LookPlan {
+    size_t at[LOOKS], words;
+};
+LookPlan look_plan(uint32_t n, uint64_t E) {
+    const DegPlan D = deg_plan(n, E);
+    const size_t hist = ((size_t)D.NB * D.nblk + SCAN_TILE - 1) / SCAN_TILE, nodes = ((size_t)n + NODE_TILE - 1) / NODE_TILE;
+    const size_t shards = D.shift <= 13 ? 0 : ((size_t)n * REV_SHARDS + SCAN_TILE - 1) / SCAN_TILE;
+    const size_t tiles[LOOKS] = {hist, hist, hist, nodes, hist, nodes, nodes, shards};
+    LookPlan P;
+    P.words = 0;
+    for (int k = 0; k < LOOKS; ++k) {
+        P.at[k] = P.words;
+        P.words += 1 + (tiles[k] ? tiles[k] : 1);
+    }
+    return P;
+}
+
 ScratchLayout scratch_layout(uint32_t n, uint64_t E) {
     ScratchLayout S;
     size_t p = 0;
@@ -1148,9 +1388,6 @@ ScratchLayout scratch_layout(uint32_t n, uint64_t E) {
     // with shard cursors (buckets wider than DEG_SUB ids); the transpose needs none
     const bool sliced = D.shift <= 13;
     const size_t nhist = (size_t)D.NB * D.nblk, nshard = sliced ? 0 : (size_t)n * REV_SHARDS;
-    size_t scan_max = nhist > nshard ? nhist : nshard;
-    scan_max = (scan_max > (size_t)n ? scan_max : (size_t)n) + 1;  // the scans over nodes too
-    const size_t nparts = (scan_max + SCAN_TILE - 1) / SCAN_TILE + 1;
     S.stats = p;
     p += align256(sizeof(BuildStats));
     S.deg = p;
@@ -1163,8 +1400,8 @@ ScratchLayout scratch_layout(uint32_t n, uint64_t E) {
     p += align256((size_t)n * 4);
     S.aoff = p;
     p += align256(((size_t)n + 1) * 4);
-    S.part = p;
-    p += align256(nparts * 4);
+    S.look = p;  // the scans' tickets and tile words
+    p += align256(8 * look_plan(n, E).words);
     S.packed = p;
     p += align256((size_t)E * 8);
     S.alt = p;
@@ -1174,7 +1411,7 @@ ScratchLayout scratch_layout(uint32_t n, uint64_t E) {
     p += align256((size_t)E * 16);
     // placement slices (bucket spans of at most DEG_SUB ids): their offsets per bucket and their
     // per-node counts, then bases
-    const uint64_t smax = sliced ? (E + SLICE_ENTRIES - 1) / SLICE_ENTRIES + D.NB : 0;
+    const uint64_t smax = sliced ? (E + slice_entries(E) - 1) / slice_entries(E) + D.NB : 0;
     S.slice_off = p;
     p += align256(((size_t)D.NB + 1) * 4);
     S.scount = p;
@@ -1195,12 +1432,9 @@ ScratchLayout scratch_layout(uint32_t n, uint64_t E) {
     return S;
 }
 
-hipError_t scan_u32(const uint32_t* in, uint64_t N, uint32_t* part, uint32_t* out, hipStream_t s) {
-    const uint32_t nb = (uint32_t)((N + SCAN_TILE - 1) / SCAN_TILE);
-    const uint32_t nbl = nb ? nb : 1;
-    hipLaunchKernelGGL(k_scan_reduce, dim3(nbl), dim3(SCAN_THREADS), 0, s, in, N, part);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, part, nbl);
-    hipLaunchKernelGGL(k_scan_down, dim3(nbl), dim3(SCAN_THREADS), 0, s, in, N, part, out);
+hipError_t scan_u32(const uint32_t* in, uint64_t N, const Look& L, uint32_t* out, hipStream_t s) {
+    const uint64_t nb = N ? (N + SCAN_TILE - 1) / SCAN_TILE : 1;
+    hipLaunchKernelGGL(k_scan, dim3((uint32_t)nb), dim3(SCAN_THREADS), 0, s, in, N, out, L);
     return hipGetLastError();
 }
 
@@ -1244,7 +1478,7 @@ rept_status rept_build_impl(uint32_t n, const uint32_t* edges, uint64_t E, void*
     uint32_t* cursor = (uint32_t*)(X + S.cursor);
     uint32_t* ahist = (uint32_t*)(X + S.ahist);
     uint32_t* aoff = (uint32_t*)(X + S.aoff);
-    uint32_t* part = (uint32_t*)(X + S.part);
+    unsigned long long* lookw = (unsigned long long*)(X + S.look);
     unsigned long long* packed = (unsigned long long*)(X + S.packed);
     unsigned long long* alt = (unsigned long long*)(X + S.alt);
     OEntry* opart = (OEntry*)(X + S.opart);
@@ -1264,11 +1498,15 @@ rept_status rept_build_impl(uint32_t n, const uint32_t* edges, uint64_t E, void*
     const uint32_t gA = grid_for(n, 2048, 512);  // node-range kernels with LDS histograms
     const DegPlan D = deg_plan(n, E);
 
-    // clear counters (fill kernels rather than memsets, so the sequence is capture-safe)
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, (uint32_t*)st,
-                       (uint64_t)(sizeof(BuildStats) / 4), 0u);
-    hipLaunchKernelGGL(k_fill_u32, dim3(gN), dim3(256), 0, s, dout, (uint64_t)n, 0u);
-    hipLaunchKernelGGL(k_fill_u32, dim3(gN), dim3(256), 0, s, ahist, (uint64_t)n, 0u);
+    const LookPlan LP = look_plan(n, E);
+    auto look = [&](int k) { return Look{(uint32_t*)(lookw + LP.at[k]), lookw + LP.at[k] + 1}; };
+    const bool sliced = D.shift <= 13;
+
+    // clear counters (a kernel rather than memsets, so the sequence is capture-safe); `cursor` counts
+    // the units placed per order key at the end, and the wide path uses it before that
+    const Clear C = {{(uint32_t*)st, (uint32_t*)lookw, deg, ahist, cursor},
+                     {sizeof(BuildStats) / 4, 2 * (uint64_t)LP.words, n, n, sliced ? n : 0u}};
+    hipLaunchKernelGGL(k_clear, dim3(grid_for(n > 2 * LP.words ? n : 2 * LP.words, 1024, cap)), dim3(256), 0, s, C);
 
     // degrees: partition endpoints by id bucket (reusing `packed` as the partition), count in LDS.
     // With many buckets the partition takes two passes: by super-buckets of 64 buckets into `alt`
@@ -1276,13 +1514,15 @@ rept_status rept_build_impl(uint32_t n, const uint32_t* edges, uint64_t E, void*
     // both passes against 7.4 ms for one, whose 4096 runs per workgroup wrote 10.2 GB for 2.1 GB
     // of ids; the 1M/20M power-law graph (245 buckets) stays faster in one pass.
     uint32_t* ends = (uint32_t*)packed;
-    if (D.NB >= 1024) {
+    if (n <= DEG_DIRECT) {
+        hipLaunchKernelGGL(k_deg_direct, dim3(D.nblk), dim3(1024), 0, s, e2, E, n, D.per_block, deg, st);
+    } else if (D.NB >= 1024) {
         const uint32_t sshift = D.shift + 6;
         const uint32_t NB1 = (uint32_t)(((uint64_t)n + ((uint64_t)1 << sshift) - 1) >> sshift);
         uint32_t* ends1 = (uint32_t*)alt;
         hipLaunchKernelGGL(k_deg_hist, dim3(D.nblk), dim3(1024), 0, s, e2, E, n, sshift, NB1, D.per_block, bhist,
                            st);
-        if (scan_u32(bhist, (uint64_t)NB1 * D.nblk, part, bscan, s) != hipSuccess) return REPT_EDEVICE;
+        if (scan_u32(bhist, (uint64_t)NB1 * D.nblk, look(LOOK_DEG1), bscan, s) != hipSuccess) return REPT_EDEVICE;
         hipLaunchKernelGGL(k_deg_scatter, dim3(D.nblk), dim3(1024), 0, s, e2, E, n, sshift, NB1, D.per_block, bscan,
                            ends1);
         // the endpoint count (the first scan's total) is kept for the second pass, whose scan
@@ -1293,19 +1533,19 @@ rept_status rept_build_impl(uint32_t n, const uint32_t* edges, uint64_t E, void*
         if (per2 == 0) per2 = 1;
         hipLaunchKernelGGL(k_ids_hist, dim3(D.nblk), dim3(1024), 0, s, ends1, &st->n_ends, D.shift, D.NB, per2,
                            bhist);
-        if (scan_u32(bhist, (uint64_t)D.NB * D.nblk, part, bscan, s) != hipSuccess) return REPT_EDEVICE;
+        if (scan_u32(bhist, (uint64_t)D.NB * D.nblk, look(LOOK_DEG2), bscan, s) != hipSuccess) return REPT_EDEVICE;
         hipLaunchKernelGGL(k_ids_scatter, dim3(D.nblk), dim3(1024), 0, s, ends1, &st->n_ends, D.shift, D.NB, per2,
                            bscan, ends);
     } else {
         hipLaunchKernelGGL(k_deg_hist, dim3(D.nblk), dim3(1024), 0, s, e2, E, n, D.shift, D.NB, D.per_block, bhist,
                            st);
-        if (scan_u32(bhist, (uint64_t)D.NB * D.nblk, part, bscan, s) != hipSuccess) return REPT_EDEVICE;
+        if (scan_u32(bhist, (uint64_t)D.NB * D.nblk, look(LOOK_DEG1), bscan, s) != hipSuccess) return REPT_EDEVICE;
         hipLaunchKernelGGL(k_deg_scatter, dim3(D.nblk), dim3(1024), 0, s, e2, E, n, D.shift, D.NB, D.per_block,
                            bscan, ends);
     }
-    hipLaunchKernelGGL(k_fill_u32, dim3(gN), dim3(256), 0, s, deg, (uint64_t)n, 0u);
-    hipLaunchKernelGGL(k_deg_count, dim3(grid_for(2 * E, DEG_SLICE, 4096)), dim3(1024), 0, s, ends, bscan, D.nblk,
-                       D.NB, D.shift, n, deg);
+    if (n > DEG_DIRECT)
+        hipLaunchKernelGGL(k_deg_count, dim3(grid_for(2 * E, DEG_SLICE, 4096)), dim3(1024), 0, s, ends, bscan,
+                           D.nblk, D.NB, D.shift, n, deg);
 
     // orientation of every edge into `alt` (free until the large-segment sort), partitioned by
     // the bucket of its lower endpoint into `opart`, whose out-degrees are counted per bucket
@@ -1313,31 +1553,31 @@ rept_status rept_build_impl(uint32_t n, const uint32_t* edges, uint64_t E, void*
     uint2* ab = (uint2*)alt;
     hipLaunchKernelGGL(k_orient_hist, dim3(D.nblk), dim3(1024), 0, s, e2, E, n, deg, D.shift, D.NB, D.per_block,
                        ab, bhist);
-    if (scan_u32(bhist, (uint64_t)D.NB * D.nblk, part, bscan, s) != hipSuccess) return REPT_EDEVICE;
+    if (scan_u32(bhist, (uint64_t)D.NB * D.nblk, look(LOOK_ORIENT), bscan, s) != hipSuccess) return REPT_EDEVICE;
     hipLaunchKernelGGL(k_orient_part, dim3(D.nblk), dim3(1024), 0, s, ab, E, D.shift, D.NB, D.per_block, bscan,
-                       opart);
+                       opart, sliced ? slice_off : (uint32_t*)nullptr, slice_entries(E));
     const uint64_t nsh = (uint64_t)n * REV_SHARDS;
     const uint32_t gS = grid_for(nsh, 256, cap);
-    const bool sliced = D.shift <= 13;
-    const uint64_t smax = (E + SLICE_ENTRIES - 1) / SLICE_ENTRIES + D.NB;
+    const uint32_t slice = slice_entries(E);
+    const uint64_t smax = (E + slice - 1) / slice + D.NB;
+    const uint32_t node_tiles = (uint32_t)(((uint64_t)n + NODE_TILE - 1) / NODE_TILE);
     if (sliced) {  // placement by slices of the partition, LDS cursors
-        hipLaunchKernelGGL(k_slice_plan, dim3(1), dim3(1024), 0, s, bscan, D.nblk, D.NB, slice_off);
         hipLaunchKernelGGL(k_slice_count<OEntry>, dim3((uint32_t)smax), dim3(1024), 0, s, (const OEntry*)opart, bscan,
                            D.nblk, D.NB,
-                           D.shift, slice_off, scount);
-        hipLaunchKernelGGL(k_slice_dout, dim3(gN), dim3(256), 0, s, scount, slice_off, D.shift, n, dout);
-        if (scan_u32(dout, n, part, off, s) != hipSuccess) return REPT_EDEVICE;
-        hipLaunchKernelGGL(k_slice_base, dim3(gN), dim3(256), 0, s, scount, slice_off, D.shift, n, off);
+                           D.shift, slice_off, slice, scount);
+        hipLaunchKernelGGL(k_slice_scan<true>, dim3(node_tiles), dim3(SCAN_THREADS), 0, s, scount, slice_off, D.shift,
+                           n, dout, off, look(LOOK_OFF), Classes{medium, large, st});
         hipLaunchKernelGGL(k_slice_place, dim3((uint32_t)smax), dim3(1024), 0, s, opart, bscan, D.nblk, D.NB,
-                           D.shift, slice_off, scount, dout, packed, (uint32_t*)nullptr, st);
+                           D.shift, slice_off, slice, scount, dout, packed, (uint32_t*)nullptr, st);
     } else {  // wider buckets: out-degrees per bucket in LDS, placement by global cursors
         hipLaunchKernelGGL(k_fill_u32, dim3(gN), dim3(256), 0, s, dout, (uint64_t)n, 0u);
         hipLaunchKernelGGL(k_out_count, dim3(grid_for(E, DEG_SLICE, 4096)), dim3(1024), 0, s, opart, bscan, D.nblk,
                            D.NB, D.shift, n, dout);
-        if (scan_u32(dout, n, part, off, s) != hipSuccess) return REPT_EDEVICE;
+        if (scan_u32(dout, n, look(LOOK_OFF), off, s) != hipSuccess) return REPT_EDEVICE;
         hipLaunchKernelGGL(k_fill_u32, dim3(gS), dim3(256), 0, s, scnt, nsh, 0u);
         hipLaunchKernelGGL(k_copy_u32, dim3(gN), dim3(256), 0, s, off, (uint64_t)n, cursor);
         hipLaunchKernelGGL(k_scatter, dim3(gE), dim3(256), 0, s, ab, E, dout, cursor, packed, scnt, st);
+        hipLaunchKernelGGL(k_classify, dim3(gA), dim3(256), 0, s, off, n, medium, large, st);
     }
     // Reverse lists.  Sliced: the sorts mark each reverse pair's source at its adjacency position
     // (in the partition's space, free after the placement) and a bucketed transpose builds the
@@ -1346,44 +1586,40 @@ rept_status rept_build_impl(uint32_t n, const uint32_t* edges, uint64_t E, void*
     uint32_t* rsrc = (uint32_t*)opart;
     RevOut RO{nullptr, rrec, rpos, rsrc};
     if (!sliced) {
-        if (scan_u32(scnt, nsh, part, sofs, s) != hipSuccess) return REPT_EDEVICE;
+        if (scan_u32(scnt, nsh, look(LOOK_SHARD), sofs, s) != hipSuccess) return REPT_EDEVICE;
         hipLaunchKernelGGL(k_rev_roff, dim3(gN), dim3(256), 0, s, sofs, n, roff, st);
         hipLaunchKernelGGL(k_copy_u32, dim3(gS), dim3(256), 0, s, sofs, nsh, scnt);  // shard cursors
         RO = RevOut{scnt, rrec, rpos, nullptr};
     }
-    hipLaunchKernelGGL(k_classify, dim3(gA), dim3(256), 0, s, off, n, medium, large, st);
-    hipLaunchKernelGGL(k_sort_small, dim3(grid_for((uint64_t)n, 256, cap)), dim3(256), 0, s, off, n, packed, nbr,
-                       tim, RO, st);
+    uint32_t per = 4;  // nodes per wavefront: at least 32 wavefronts per CU, if there are nodes for them
+    while (per < 64 && (uint64_t)per * 32 * (cus ? cus : 256) < n) per <<= 1;
+    hipLaunchKernelGGL(k_sort_small, dim3(grid_for((uint64_t)n, 4 * per, cap)), dim3(256), 0, s, off, n, per, packed,
+                       nbr, tim, RO, st);
     hipLaunchKernelGGL(k_sort_wave, dim3(cus ? cus * 8 : 2048), dim3(256), 0, s, off, medium, packed, nbr, tim,
                        RO, st);
-    hipLaunchKernelGGL(k_sort_medium, dim3(cus ? cus * 4 : 1024), dim3(512), 0, s, off, medium, n, packed, nbr,
-                       tim, RO, st);
     uint32_t id_bits = 1;
     while (id_bits < 32 && ((uint64_t)1 << id_bits) < (uint64_t)n) ++id_bits;
-    hipLaunchKernelGGL(k_sort_large, dim3(cus ? cus : 256), dim3(64), 0, s, off, large, packed, alt, id_bits,
-                       nbr, tim, RO, st);
+    hipLaunchKernelGGL(k_sort_rest, dim3(cus ? cus * 4 : 1024), dim3(512), 0, s, off, medium, large, n, packed, alt,
+                       id_bits, nbr, tim, RO, st);
     if (sliced) {
         // the reverse pairs (b, a, t, p) partitioned by the bucket of b into the sort buffers
         // (`packed` and `alt`, 16 bytes per edge together, free after the sorts)
         uint4* rpart = (uint4*)packed;
-        uint32_t* rcnt = cursor;
         hipLaunchKernelGGL(k_rev_hist, dim3(D.nblk), dim3(1024), 0, s, rsrc, nbr, off, n, D.shift, D.NB,
                            D.per_block, bhist);
-        if (scan_u32(bhist, (uint64_t)D.NB * D.nblk, part, bscan, s) != hipSuccess) return REPT_EDEVICE;
+        if (scan_u32(bhist, (uint64_t)D.NB * D.nblk, look(LOOK_REV), bscan, s) != hipSuccess) return REPT_EDEVICE;
         hipLaunchKernelGGL(k_rev_part, dim3(D.nblk), dim3(1024), 0, s, rsrc, nbr, tim, off, n, D.shift, D.NB,
-                           D.per_block, bscan, rpart);
-        hipLaunchKernelGGL(k_slice_plan, dim3(1), dim3(1024), 0, s, bscan, D.nblk, D.NB, slice_off);
+                           D.per_block, bscan, rpart, slice_off, slice);
         hipLaunchKernelGGL(k_slice_count<uint4>, dim3((uint32_t)smax), dim3(1024), 0, s, (const uint4*)rpart, bscan,
-                           D.nblk, D.NB, D.shift, slice_off, scount);
-        hipLaunchKernelGGL(k_slice_dout, dim3(gN), dim3(256), 0, s, scount, slice_off, D.shift, n, rcnt);
-        if (scan_u32(rcnt, n, part, roff, s) != hipSuccess) return REPT_EDEVICE;
-        hipLaunchKernelGGL(k_slice_base, dim3(gN), dim3(256), 0, s, scount, slice_off, D.shift, n, roff);
+                           D.nblk, D.NB, D.shift, slice_off, slice, scount);
+        hipLaunchKernelGGL(k_slice_scan<false>, dim3(node_tiles), dim3(SCAN_THREADS), 0, s, scount, slice_off, D.shift,
+                           n, (uint32_t*)nullptr, roff, look(LOOK_ROFF), Classes{nullptr, nullptr, nullptr});
         hipLaunchKernelGGL(k_rev_place, dim3((uint32_t)smax), dim3(1024), 0, s, (const uint4*)rpart, bscan, D.nblk,
-                           D.NB, D.shift, slice_off, scount, off, rrec, rpos);
+                           D.NB, D.shift, slice_off, slice, scount, off, rrec, rpos);
     }
     hipLaunchKernelGGL(k_apex_hist, dim3(gA), dim3(256), 0, s, off, roff, deg, n, ahist, st);
-    if (scan_u32(ahist, n, part, aoff, s) != hipSuccess) return REPT_EDEVICE;
-    hipLaunchKernelGGL(k_fill_u32, dim3(gN), dim3(256), 0, s, cursor, (uint64_t)n, 0u);
+    if (scan_u32(ahist, n, look(LOOK_APEX), aoff, s) != hipSuccess) return REPT_EDEVICE;
+    if (!sliced) hipLaunchKernelGGL(k_fill_u32, dim3(gN), dim3(256), 0, s, cursor, (uint64_t)n, 0u);
     hipLaunchKernelGGL(k_apex_scatter, dim3(gA), dim3(256), 0, s, off, roff, n, deg, aoff, cursor,
                        apex, (uint32_t*)(P + L.ctrl + kHubOffset), st);
     if (hipGetLastError() != hipSuccess) return REPT_EDEVICE;
@@ -1408,11 +1644,13 @@ rept_status rept_build_impl(uint32_t n, const uint32_t* edges, uint64_t E, void*
     g->roff = roff;
     g->rrec = rrec;
     g->rpos = rpos;
-    g->num_apex = hs.num_apex;
-    g->max_out = hs.max_out;
+    for (const StatPart& P : hs.part) {
+        g->num_apex += P.num_apex;
+        g->max_out = P.max_out > g->max_out ? P.max_out : g->max_out;
+        g->work += P.work;
+        g->sum_out_sq += P.sum_out_sq;
+    }
     g->num_rev = hs.num_rev;
-    g->work = hs.work;
-    g->sum_out_sq = hs.sum_out_sq;
     memcpy(g->above, hs.above, sizeof(g->above));
     g->hubs = (const uint32_t*)(P + L.ctrl + kHubOffset);
     g->n_hub = hs.n_hub;
