@@ -1655,7 +1655,19 @@ __global__ void __launch_bounds__(phases == 2u ? kLightThreads : 1024u, phases =
             }
         }
     }
-    flush_hist(J, V, cur);
+    if (njobs == 1) {
+        // one job: the wavefronts' counts are summed first (one update per workgroup and processor)
+        __syncthreads();
+        if (HC)
+            for (uint32_t p = threadIdx.x; p < jobs[0].c; p += blockDim.x) {
+                uint64_t v = 0;
+                for (uint32_t w = 0; w < nw; ++w)
+                    v += ((const uint32_t*)(lds + L.misc_off + w * L.misc.bytes + L.misc.hist))[p];
+                if (v) add64(jobs[0].global + p, v);
+            }
+    } else {
+        flush_hist(J, V, cur);
+    }
     if (hub_job >= 0) hub_flush(jobs[hub_job], hub);
 }
 
