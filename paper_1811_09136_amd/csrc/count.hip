@@ -899,6 +899,13 @@ __device__ __forceinline__ void walk_chunk(const JobRegs& J, const TeamView& T, 
     wave_sync();
 }
 
+// Apexes with this many out-neighbours and more have long lists to walk (the b's rank above a), so
+// that a chunk's walk outlasts the taking of it: their chunks shrink to kChunkMin lists towards the
+// unit's end, so that its wavefronts end together.  Below it the smaller chunks cost more than the
+// wait: with every unit split so, R-MAT scale 24 gains the same 6% (209.7 to 197.7 ms), but the
+// 20M-edge power law loses 1.2% (7.84 to 7.94 ms) and 32 jobs of 500k edges 3% (1.17 to 1.21 ms);
+// from 384 on, 209.7 to 199.7 ms and neither of the others moves.
+constexpr uint32_t kLong = 384, kChunkMin = 16;
 constexpr uint32_t kRoundLists = 1u << 15;  // lists walked between flushes of the W entries' counts
 
 // Count every triangle whose lowest-ranked node is a.  The team is the workgroup (BLOCK) or
@@ -960,9 +967,9 @@ __device__ __forceinline__ void count_apex(const JobRegs& J, const TeamView& T, 
         team_sync<BLOCK>();
         if (BLOCK && ws == 0 && (threadIdx.x >> 6) == nw - 1u) ahead();
         const uint32_t no = whole ? wave_uni(*nown) : o1 - o0, lists = no + nr;
-        // lists per chunk: a few lists are spread over all wavefronts, 16 to a chunk at least
+        // Lists per chunk: a few lists are spread over all wavefronts, 16 to a chunk at least; under a
+        // long apex (kLong), half a wavefront's share of what is left
         const uint32_t even = ((lists + nw - 1u) / nw + 15u) & ~15u;
-        const uint32_t db = even < T.DB ? even : T.DB;  // (T.DB <= 64: one list per lane)
         // A W entry's 16-bit counts gain at most one per list, so they are flushed every kRoundLists.
         for (uint32_t es = 0; es < lists; ) {
             const uint32_t ee = lists - es > kRoundLists ? es + kRoundLists : lists;
@@ -970,15 +977,25 @@ __device__ __forceinline__ void count_apex(const JobRegs& J, const TeamView& T, 
                 if (BLOCK && tid == 0) *next = 0;
                 team_sync<BLOCK>();
             }
-            for (uint32_t seq = 0;; ++seq) {
-                uint32_t c = seq;
+            for (uint32_t at = es;;) {
+                uint32_t db = T.DB;  // (at most 64: one list per lane)
                 if (BLOCK) {
-                    if (lane == 0) c = atomicAdd(next, 1u);
-                    c = lane_val(c, 0);
+                    if (lane == 0) {
+                        db = even;
+                        if (d >= kLong) {
+                            const uint32_t seen = *(volatile uint32_t*)next, all = ee - es;
+                            db = (all > seen ? all - seen : 0u) / (2u * nw);
+                            db = db < kChunkMin ? kChunkMin : db;
+                        }
+                        db = db < T.DB ? db : T.DB;
+                        at = es + atomicAdd(next, db);
+                    }
+                    at = lane_val(at, 0);
+                    db = lane_val(db, 0);
                 }
-                const uint64_t first = (uint64_t)es + (uint64_t)c * db;
-                if (first >= ee) break;
-                const uint32_t x = (uint32_t)first + lane;
+                if (at >= ee) break;
+                const uint32_t x = at + lane;
+                if (!BLOCK) at += db;
                 uint32_t b = 0, bo = 0, bd = 0, tb = 0, pab = 0;
                 uint64_t lo = 0, hi = 0;
                 if (lane < db && x < ee) {

@@ -100,3 +100,16 @@ def test_unit_with_many_reverse_lists(cuda, lists):
         want[[0, 1]] = lists
         want[y] = 1
         assert np.array_equal(l[0], want), shape
+
+
+@pytest.mark.parametrize("nodes", [383, 384, 385, 386, 640, 1100])
+def test_chunks_under_long_apexes(cuda, nodes):
+    """A clique's apexes have every out-degree below `nodes`, and as many lists: chunks of even size
+    below 384, shrinking ones from there (m = 1 counts every triangle once)."""
+    from paper_1811_09136_amd import rept
+    e = synth.shuffled(synth.complete(nodes), 3, flip_seed=4).astype(np.uint32)
+    for shape in (dict(), dict(blocks=1), dict(wave_cap=8, blocks=3), dict(threads=128, wave_cap=8)):
+        print("[case]", nodes, shape, flush=True)
+        g, l = _count(cuda, e, nodes, rept.Params(1, 1, 9), shape)
+        assert int(g[0]) == nodes * (nodes - 1) * (nodes - 2) // 6, shape
+        assert (l[0] == (nodes - 1) * (nodes - 2) // 2).all(), shape
