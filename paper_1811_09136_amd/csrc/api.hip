@@ -123,7 +123,7 @@ rept_status recount_window(rept_stream* h, uint64_t t0, uint64_t t1, hipStream_t
 }
 
 struct IncLayout {
-    size_t key[2], tim[2], off, coff, ckey_a, ckey_b, ctim_a, ctim_b, end, flags, temp, total, temp_bytes;
+    size_t key[2], tim[2], off, noff, ckey_a, ckey_b, ctim_a, ctim_b, end, flags, temp, total, temp_bytes;
     size_t eall, gpers, gscr, gws, gpers_bytes, gscr_bytes, gws_bytes;
 };
 size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -136,13 +136,13 @@ IncLayout inc_layout(uint32_t n, uint64_t cap, uint64_t maxc) {
         L.tim[i] = p; p = up256(p + 4 * E2);
     }
     L.off = p; p = up256(p + 4 * ((size_t)n + 1));
-    L.coff = p; p = up256(p + 4 * ((size_t)n + 1));
+    L.noff = p; p = up256(p + 4 * ((size_t)n + 1));
     L.ckey_a = p; p = up256(p + 8 * C2);
     L.ckey_b = p; p = up256(p + 8 * C2);
     L.ctim_a = p; p = up256(p + 4 * C2);
     L.ctim_b = p; p = up256(p + 4 * C2);
     L.end = p; p = up256(p + 8 * C2);
-    L.flags = p; p = up256(p + 8);
+    L.flags = p; p = up256(p + 16);
     L.temp_bytes = rept_inc_sort_temp_bytes(C2, 64);
     L.temp = p; p = up256(p + L.temp_bytes);
     // the windowed recount: the stream in arrival order, a built graph of up to `cap` edges with
@@ -1137,7 +1137,7 @@ rept_status rept_stream_create(uint32_t n, uint64_t capacity, uint64_t max_chunk
         S.tim[i] = (uint32_t*)(B + L.tim[i]);
     }
     S.off = (uint32_t*)(B + L.off);
-    S.coff = (uint32_t*)(B + L.coff);
+    S.noff = (uint32_t*)(B + L.noff);
     S.ckey_a = (uint64_t*)(B + L.ckey_a);
     S.ckey_b = (uint64_t*)(B + L.ckey_b);
     S.ctim_a = (uint32_t*)(B + L.ctim_a);
@@ -1196,28 +1196,22 @@ rept_status rept_stream_append(rept_stream* h, const uint32_t* edges, uint64_t n
     if (temp == 0) return REPT_EDEVICE;
     if (temp > h->st.temp_bytes) return REPT_ENOMEM;  // not expected: sized for the largest chunk
     hipStream_t s = (hipStream_t)stream;
-    if (rept_inc_prepare(h->st, edges, num_edges, s) != hipSuccess) return REPT_EDEVICE;
-    uint32_t flags = 0;
-    if (hipMemcpyAsync(&flags, h->st.flags, sizeof(flags), hipMemcpyDeviceToHost, s) != hipSuccess ||
+    const uint64_t t0 = h->st.T;
+    struct {
+        uint32_t flags, pad;
+        uint64_t items;
+    } seen = {0, 0, 0};
+    if (rept_inc_prepare(h->st, edges, num_edges, h->eall + 2 * t0, s) != hipSuccess ||
+        hipMemcpyAsync(&seen, h->st.flags, sizeof(seen), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
         return REPT_EDEVICE;
     // the stream's own order of precedence: ids, then self-loops, then repeated pairs
-    if (flags & RF_RANGE) return REPT_ERANGE;
-    if (flags & RF_SELFLOOP) return REPT_ESELFLOOP;
-    if (flags & RF_DUP) return REPT_EDUP;
-    const uint64_t t0 = h->st.T;
-    if (hipMemcpyAsync(h->eall + 2 * t0, edges, 8 * num_edges, hipMemcpyDeviceToDevice, s) != hipSuccess ||
-        rept_inc_merge(h->st, num_edges, s) != hipSuccess)
-        return REPT_EDEVICE;
-    bool recount = h->policy == REPT_STREAM_RECOUNT;
-    if (h->policy == REPT_STREAM_AUTO) {
-        uint64_t items = 0;
-        if (hipMemcpyAsync(&items, h->st.end + 2 * num_edges - 1, sizeof(items), hipMemcpyDeviceToHost, s) !=
-                hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess)
-            return REPT_EDEVICE;
-        recount = items > kRecountItemsPerEdge * h->st.T;
-    }
+    if (seen.flags & RF_RANGE) return REPT_ERANGE;
+    if (seen.flags & RF_SELFLOOP) return REPT_ESELFLOOP;
+    if (seen.flags & RF_DUP) return REPT_EDUP;
+    rept_inc_accept(h->st, num_edges);
+    const bool recount = h->policy == REPT_STREAM_RECOUNT ||
+                         (h->policy == REPT_STREAM_AUTO && seen.items > kRecountItemsPerEdge * h->st.T);
     if (recount) {
         const rept_status st = recount_window(h, t0, h->st.T, s);
         if (st == REPT_OK) {

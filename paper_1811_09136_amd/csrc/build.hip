@@ -13,10 +13,16 @@
 #include <string.h>
 
 #include "common.h"
+#include "scan.h"
 
 namespace {
 
-constexpr int SCAN_THREADS = 256;
+using scan::block_excl_scan;
+using scan::Look;
+using scan::look_back;
+using scan::look_ticket;
+
+constexpr int SCAN_THREADS = scan::kScanThreads;
 constexpr int SCAN_ITEMS = 16;
 constexpr int SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
 constexpr int NODE_ITEMS = 4;
@@ -37,24 +43,6 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
         if (lane >= d) v += o;
     }
     return v;
-}
-
-// exclusive scan of one value per thread over a 256-thread block; returns the block total
-__device__ uint32_t block_excl_scan256(uint32_t v, uint32_t& total) {
-    __shared__ uint32_t wsum[SCAN_THREADS / 64];
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    uint32_t inc = wave_incl_scan(v);
-    if (lane == 63) wsum[wid] = inc;
-    __syncthreads();
-    uint32_t base = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < SCAN_THREADS / 64; ++w) {
-        if (w < wid) base += wsum[w];
-        tot += wsum[w];
-    }
-    __syncthreads();
-    total = tot;
-    return base + inc - v;
 }
 
 template <typename T>
@@ -89,61 +77,6 @@ __device__ uint32_t block_max256(uint32_t v) {  // valid in thread 0
 }
 
 // ---------------------------------------------------------------- exclusive scan (u32) ----
-// One launch per scan.  A workgroup takes the next tile by a ticket, sums it, publishes the sum and
-// adds up the sums of the tiles before it (wavefront 0, 64 tiles at a look) until it meets one that
-// has published its inclusive sum.  It only ever waits for tiles whose tickets were drawn before its
-// own, so their workgroups are running and every wait ends.  A tile's word holds its state and its sum
-// together, so no other ordering is needed.  (The three launches of a reduce-then-scan cost a small
-// graph more than the work: a build of 2,000 nodes took seven scans, 21 of its 47 launches.)
-struct Look {
-    uint32_t* ticket;
-    unsigned long long* tile;  // state << 32 | sum; 0: nothing yet
-};
-constexpr unsigned long long kTileSum = 1ull << 32, kTileIncl = 2ull << 32;
-
-__device__ __forceinline__ uint32_t look_ticket(const Look& L) {
-    __shared__ uint32_t t;
-    __syncthreads();
-    if (threadIdx.x == 0) t = atomicAdd(L.ticket, 1u);
-    __syncthreads();
-    return t;
-}
-
-// the sum of all tiles before `t`, given this tile's sum (every thread of a 256-thread workgroup)
-__device__ uint32_t look_back(const Look& L, uint32_t t, uint32_t sum) {
-    __shared__ uint32_t before;
-    const int lane = threadIdx.x & 63;
-    if (threadIdx.x < 64) {
-        if (lane == 0 && t)
-            __hip_atomic_store(&L.tile[t], kTileSum | sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        uint32_t acc = 0;
-        for (int64_t at = (int64_t)t - 1; at >= 0;) {
-            const int64_t i = at - lane;
-            const unsigned long long w =
-                i >= 0 ? __hip_atomic_load(&L.tile[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kTileIncl;
-            const unsigned long long incl = __ballot(w >= kTileIncl), none = __ballot(w < kTileSum);
-            const int first = incl ? __builtin_ctzll(incl) : 63;  // the lanes 0 .. first are added up
-            if (none & (~0ull >> (63 - first))) {
-                __builtin_amdgcn_s_sleep(1);
-                continue;
-            }
-            uint32_t v = lane <= first ? (uint32_t)w : 0u;
-#pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-            acc += v;
-            if (incl) break;
-            at -= 64;
-        }
-        if (lane == 0) {
-            __hip_atomic_store(&L.tile[t], kTileIncl | (uint32_t)(acc + sum), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-            before = acc;
-        }
-    }
-    __syncthreads();
-    return before;
-}
-
 // out[i] = sum of in[0..i), out[N] = total (`in` and `out` 16-byte aligned)
 __global__ void __launch_bounds__(SCAN_THREADS) k_scan(const uint32_t* __restrict__ in, uint64_t N,
                                                         uint32_t* __restrict__ out, Look L) {
@@ -162,7 +95,7 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan(const uint32_t* __restric
 #pragma unroll
     for (int r = 0; r < SCAN_ITEMS; ++r) s += v[r];
     uint32_t total;
-    uint32_t pre = block_excl_scan256(s, total);
+    uint32_t pre = block_excl_scan(s, total);
     pre += look_back(L, t, total);
 #pragma unroll
     for (int r = 0; r < SCAN_ITEMS; ++r) {
@@ -596,7 +529,7 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_slice_scan(uint32_t* __restric
         }
     }
     uint32_t total;
-    uint32_t pre = block_excl_scan256(d[0] + d[1] + d[2] + d[3], total);
+    uint32_t pre = block_excl_scan(d[0] + d[1] + d[2] + d[3], total);
     pre += look_back(L, t, total);
     uint32_t run[4];
 #pragma unroll

@@ -227,14 +227,26 @@ struct IncState {
     uint64_t* key[2];
     uint32_t* tim[2];
     uint32_t* off;   // [n + 1] offsets into the current copy
-    uint32_t* coff;  // [n + 1] first position of each node's run in the sorted chunk
-    uint64_t *ckey_a, *ckey_b;  // chunk keys before / after the sort (a: item lengths later)
+    uint32_t* noff;  // [n + 1] offsets into the other copy, which takes the merge with a chunk
+    uint64_t *ckey_a, *ckey_b;  // the chunk sort's two buffers (the sorted chunk is in b)
     uint32_t *ctim_a, *ctim_b;
     uint64_t* end;      // inclusive scan of the item lengths
-    uint32_t* flags;    // validation word (RF_*)
+    uint32_t* flags;    // validation word (RF_*), and 8 bytes on the chunk's work items
+    bool flags_clear;   // the validation word is known to be zero
     void* temp;         // temporary storage of the chunk sort and the scans
     size_t temp_bytes;
     uint32_t count_blocks;
+};
+// Arguments of the kernel that makes a chunk's keys
+struct IncChunk {
+    uint64_t W;
+    uint32_t n, T;  // T: the first edge's time
+    uint64_t* ckey;
+    uint32_t* ctim;
+    uint2* eall;  // takes the chunk's edges in order
+    uint32_t* flags;
+    unsigned long long* look;  // words of the scans to come, to be cleared
+    uint32_t look_words;
 };
 // Arguments of the per-edge counting kernel
 struct IncCount {
@@ -251,15 +263,14 @@ struct IncCount {
     uint32_t ck_full, last_ck, pstride, per_proc;  // processor map as in JobDev
     uint64_t hp[4 * REPT_GMAX];
 };
-// temporary bytes for sorting `entries` keys of end_bit bits and scanning as many lengths (the
-// library's own radix sort and scans; 0 on failure)
+// temporary bytes for sorting the 2W `entries` of a chunk and for the scans (end_bit as in IncState)
 size_t rept_inc_sort_temp_bytes(uint64_t entries, uint32_t end_bit);
 hipError_t rept_inc_zero64(void* p, uint64_t words, hipStream_t stream);
-// steps 1-3 of an append (keys, sort, validation, chunk runs); the state is not changed
-hipError_t rept_inc_prepare(const IncState& st, const uint32_t* edges, uint64_t W, hipStream_t stream);
-// step 4: merge the chunk into the adjacency and scan the chunk's work items (one per entry of
-// the shorter list of each chunk edge's endpoints; the total is st.end[2W - 1]); advances st.cur
-// and st.T
-hipError_t rept_inc_merge(IncState& st, uint64_t W, hipStream_t stream);
-// step 5: count each chunk edge against the edges that arrived before it (after rept_inc_merge)
+// steps 1-4 of an append: keys, sort, merge into the other copy, validation word, work items (one per
+// entry of the shorter list of each chunk edge's endpoints, their total beside the validation word);
+// the chunk's edges are copied to `eall`.  The current adjacency is not changed.
+hipError_t rept_inc_prepare(IncState& st, const uint32_t* edges, uint64_t W, uint32_t* eall, hipStream_t stream);
+// the validation word was read as zero: the merged copy becomes the current one (st.T advances)
+void rept_inc_accept(IncState& st, uint64_t W);
+// step 5: count each chunk edge against the edges that arrived before it (after rept_inc_accept)
 hipError_t rept_inc_count(const IncState& st, uint64_t W, const IncCount& base, hipStream_t stream);

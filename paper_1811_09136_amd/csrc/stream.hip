@@ -5,15 +5,17 @@
 // State on the device: the whole adjacency of the edges seen so far, both directions, as one
 // array of keys (x << 32 | y) sorted by (x, y) with the arrival time of each edge beside it,
 // and the node offsets into it.  An append:
-//   1. turns the chunk into keys (both directions, times T .. T+W-1) and checks ids and
-//      self-loops;
-//   2. sorts the chunk's keys (a stable LSD radix sort of 8-bit digits over the key bits that can
-//      be set);
-//   3. checks for an unordered pair twice in the chunk or already in the adjacency (binary
-//      search in the node's sorted list), and finds each node's run in the sorted chunk;
-//   4. after the host has read the validation word (the one synchronisation), merges the chunk
-//      into the adjacency: every old and every new entry computes its merged position by one
-//      binary search in the other side's run of the same node, so the merge is one pass;
+//   1. turns the chunk into keys (both directions, times T .. T+W-1), checks ids and self-loops,
+//      copies the edges to the stream in arrival order, and sorts the keys: a small chunk by
+//      comparing every pair of keys, others by a stable LSD radix sort over the id bits;
+//   2. finds each node's run in the sorted chunk, which gives the merged offsets (in a second array);
+//   3. merges the chunk into the other copy of the adjacency: every old and every new entry computes
+//      its merged position by one binary search in the other side's run of the same node, so the
+//      merge is one pass.  A new entry's search also shows whether its pair is there already; its
+//      neighbour in the sorted chunk, whether the pair is in the chunk twice;
+//   4. scans the chunk's work items (below).  The host then reads the validation word and the number
+//      of items together (the one synchronisation) and, if the chunk is valid, takes the merged copy
+//      and offsets as the current ones.  A refused chunk has written nothing that is read again;
 //   5. counts the chunk's edges: for the edge (u, v) at time t, the entries w of the shorter of
 //      the two lists that arrived before t are searched in the other list (arrived before t as
 //      well); each common neighbour is a triangle whose last edge is (u, v), and every group
@@ -25,6 +27,7 @@
 
 #include "common.h"
 #include "edge_hash.h"
+#include "scan.h"
 
 namespace {
 
@@ -45,105 +48,148 @@ __device__ __forceinline__ uint64_t lower_bound64(const uint64_t* __restrict__ k
     return lo;
 }
 
-// 1. chunk edges -> keys of both directions, times; invalid ids are flagged and replaced by
-// node 0 so that every later index stays in range (the append is refused anyway)
-__global__ void __launch_bounds__(kThreads) k_inc_keys(const uint2* __restrict__ edges, uint64_t W, uint32_t n,
-                                                       uint32_t T, uint64_t* __restrict__ key,
-                                                       uint32_t* __restrict__ tim, uint32_t* __restrict__ flags) {
-    uint32_t f = 0;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < W; i += (uint64_t)gridDim.x * blockDim.x) {
-        uint2 e = edges[i];
-        if (e.x >= n || e.y >= n) {
-            f |= RF_RANGE;
-            e = make_uint2(0u, 0u);
-        } else if (e.x == e.y) {
-            f |= RF_SELFLOOP;
-        }
-        key[2 * i] = ((uint64_t)e.x << 32) | e.y;
-        key[2 * i + 1] = ((uint64_t)e.y << 32) | e.x;
-        tim[2 * i] = tim[2 * i + 1] = T + (uint32_t)i;
+__device__ __forceinline__ uint32_t edge_flags(uint2& e, uint32_t n) {
+    if (e.x >= n || e.y >= n) {  // replaced by node 0: every later index stays in range (the append is refused)
+        e = make_uint2(0u, 0u);
+        return RF_RANGE;
     }
-    if (f) atomicOr(flags, f);
+    return e.x == e.y ? (uint32_t)RF_SELFLOOP : 0u;
+}
+__device__ __forceinline__ uint64_t edge_key(uint2 e, bool rev) {
+    return rev ? ((uint64_t)e.y << 32) | e.x : ((uint64_t)e.x << 32) | e.y;
 }
 
-// 3a. a pair twice in the sorted chunk, or already in the adjacency
-__global__ void __launch_bounds__(kThreads) k_inc_check(const uint64_t* __restrict__ ck, uint64_t N2,
-                                                        const uint64_t* __restrict__ akey,
+// 1a. A small chunk's sort, one launch: a key's position is the number of keys below it, equal keys in
+// order of arrival.  A workgroup takes 64 entries, one per lane; its wavefronts share the chunk's
+// edges, whose keys they make from scalar loads.  Bound by the compares, (2W)^2 of them over all SIMDs.
+// 1,000 edges: 11 us (the radix sort's 20 launches, four digits of 8 bits: 120 us).
+constexpr uint32_t kRankThreads = 1024, kRankWaves = kRankThreads / 64;
+__global__ void __launch_bounds__(kRankThreads) k_inc_rank(const uint2* __restrict__ edges, IncChunk a) {
+    __shared__ uint32_t below[kRankWaves][64];
+    const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint32_t W = (uint32_t)a.W, i0 = blockIdx.x * 64, i = i0 + lane;
+    for (uint32_t k = blockIdx.x * kRankThreads + threadIdx.x; k < a.look_words; k += gridDim.x * kRankThreads)
+        a.look[k] = 0ull;
+    uint32_t f = 0;
+    uint2 own = edges[(i >> 1) < W ? i >> 1 : W - 1];
+    if (w == 0 && i < 2 * W) {
+        if (!(i & 1u)) a.eall[i >> 1] = own;
+        f = edge_flags(own, a.n);
+    } else {
+        (void)edge_flags(own, a.n);
+    }
+    const uint64_t key = edge_key(own, i & 1u);
+    const uint32_t share = (W + kRankWaves - 1) / kRankWaves;
+    const uint32_t e0 = __builtin_amdgcn_readfirstlane(w * share < W ? w * share : W);
+    const uint32_t e1 = W - e0 < share ? W : e0 + share;
+    const uint32_t o0 = i0 >> 1, o1 = o0 + 32;  // the workgroup's own edges
+    uint32_t lt = 0;
+    const uint32_t b1 = e1 < o0 ? e1 : o0;
+#pragma unroll 8
+    for (uint32_t j = e0; j < b1; ++j) {  // arrived before: equal keys count
+        uint2 e = edges[j];
+        (void)edge_flags(e, a.n);
+        lt += edge_key(e, false) <= key;
+        lt += edge_key(e, true) <= key;
+    }
+    const uint32_t m0 = e0 > o0 ? e0 : o0, m1 = e1 < o1 ? e1 : o1;
+    for (uint32_t j = m0; j < m1; ++j) {
+        uint2 e = edges[j];
+        (void)edge_flags(e, a.n);
+        const uint64_t k0 = edge_key(e, false), k1 = edge_key(e, true);
+        lt += k0 < key || (k0 == key && 2 * j < i);
+        lt += k1 < key || (k1 == key && 2 * j + 1 < i);
+    }
+    const uint32_t a0 = e0 > o1 ? e0 : o1;
+#pragma unroll 8
+    for (uint32_t j = a0; j < e1; ++j) {
+        uint2 e = edges[j];
+        (void)edge_flags(e, a.n);
+        lt += edge_key(e, false) < key;
+        lt += edge_key(e, true) < key;
+    }
+    below[w][lane] = lt;
+    __syncthreads();
+    if (w == 0 && i < 2 * W) {
+        uint32_t at = 0;
+#pragma unroll
+        for (uint32_t v = 0; v < kRankWaves; ++v) at += below[v][lane];
+        a.ckey[at] = key;
+        a.ctim[at] = a.T + (i >> 1);
+    }
+    if (f) atomicOr(a.flags, f);
+}
+
+// 2. noff[x] = off[x] + the first chunk position with node >= x, for x in [0, n]
+__global__ void __launch_bounds__(kThreads) k_inc_noff(const uint64_t* __restrict__ ck, uint64_t N2, uint32_t n,
+                                                       const uint32_t* __restrict__ off, uint32_t* __restrict__ noff) {
+    for (uint64_t x = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; x <= n; x += (uint64_t)gridDim.x * blockDim.x)
+        noff[x] = off[x] + (uint32_t)lower_bound64(ck, 0, N2, x << 32);
+}
+
+// 3. Entries [0, N) are the old ones: an entry moves up by the number of chunk entries of its node
+// with a smaller key.  Entries [N, N + N2) are the chunk's, which land after the old entries of their
+// node with a smaller key; a pair twice in the chunk or already in the adjacency is flagged.
+__global__ void __launch_bounds__(kThreads) k_inc_merge(const uint64_t* __restrict__ akey,
+                                                        const uint32_t* __restrict__ atim, uint64_t N,
+                                                        const uint64_t* __restrict__ ck,
+                                                        const uint32_t* __restrict__ ct, uint64_t N2,
                                                         const uint32_t* __restrict__ off,
-                                                        uint32_t* __restrict__ flags) {
+                                                        const uint32_t* __restrict__ noff, uint64_t* __restrict__ okey,
+                                                        uint32_t* __restrict__ otim, uint32_t* __restrict__ flags) {
     uint32_t f = 0;
-    for (uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; p < N2; p += (uint64_t)gridDim.x * blockDim.x) {
-        const uint64_t k = ck[p];
-        if (p && ck[p - 1] == k) f |= RF_DUP;
-        const uint32_t x = hi32(k);
-        const uint64_t s = off[x], e = off[x + 1];
-        const uint64_t j = lower_bound64(akey, s, e, k);
-        if (j < e && akey[j] == k) f |= RF_DUP;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N + N2;
+         i += (uint64_t)gridDim.x * blockDim.x) {
+        if (i < N) {
+            const uint64_t k = akey[i];
+            const uint32_t x = hi32(k), c0 = noff[x] - off[x], c1 = noff[x + 1] - off[x + 1];
+            // off[x] + c0 + (i - off[x]) + (chunk entries of x with a smaller key)
+            const uint64_t q = i + lower_bound64(ck, c0, c1, k);
+            okey[q] = k;
+            otim[q] = atim[i];
+        } else {
+            const uint64_t p = i - N, k = ck[p];
+            const uint32_t x = hi32(k);
+            const uint64_t e = off[x + 1], r = lower_bound64(akey, off[x], e, k);
+            if ((p && ck[p - 1] == k) || (r < e && akey[r] == k)) f |= RF_DUP;
+            okey[p + r] = k;  // off[x] + c0 + (p - c0) + (r - off[x])
+            otim[p + r] = ct[p];
+        }
     }
     if (f) atomicOr(flags, f);
 }
 
-// 3b. coff[x] = first chunk position with node >= x, for x in [0, n]
-__global__ void __launch_bounds__(kThreads) k_inc_coff(const uint64_t* __restrict__ ck, uint64_t N2, uint32_t n,
-                                                       uint32_t* __restrict__ coff) {
-    for (uint64_t x = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; x <= n; x += (uint64_t)gridDim.x * blockDim.x)
-        coff[x] = (uint32_t)lower_bound64(ck, 0, N2, x << 32);
-}
-
-// 4a. old entries move up by the number of chunk entries of their node with a smaller key
-__global__ void __launch_bounds__(kThreads) k_inc_merge_old(const uint64_t* __restrict__ akey,
-                                                            const uint32_t* __restrict__ atim, uint64_t N,
-                                                            const uint32_t* __restrict__ off,
-                                                            const uint32_t* __restrict__ coff,
-                                                            const uint64_t* __restrict__ ck,
-                                                            uint64_t* __restrict__ okey, uint32_t* __restrict__ otim) {
-    for (uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; p < N; p += (uint64_t)gridDim.x * blockDim.x) {
-        const uint64_t k = akey[p];
-        const uint32_t x = hi32(k);
-        const uint64_t r = lower_bound64(ck, coff[x], coff[x + 1], k) - coff[x];
-        const uint64_t q = p + coff[x] + r;  // off[x] + coff[x] + (p - off[x]) + r
-        okey[q] = k;
-        otim[q] = atim[p];
-    }
-}
-
-// 4b. chunk entries land after the old entries of their node with a smaller key
-__global__ void __launch_bounds__(kThreads) k_inc_merge_new(const uint64_t* __restrict__ ck,
-                                                            const uint32_t* __restrict__ ct, uint64_t N2,
-                                                            const uint32_t* __restrict__ off,
-                                                            const uint64_t* __restrict__ akey,
-                                                            uint64_t* __restrict__ okey, uint32_t* __restrict__ otim) {
-    for (uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; p < N2; p += (uint64_t)gridDim.x * blockDim.x) {
-        const uint64_t k = ck[p];
-        const uint32_t x = hi32(k);
-        const uint64_t r = lower_bound64(akey, off[x], off[x + 1], k) - off[x];
-        const uint64_t q = off[x] + p + r;  // off[x] + coff[x] + (p - coff[x]) + r
-        okey[q] = k;
-        otim[q] = ct[p];
-    }
-}
-
-// 4c. merged offsets: off[x] += coff[x]
-__global__ void __launch_bounds__(kThreads) k_inc_off(uint32_t* __restrict__ off, const uint32_t* __restrict__ coff,
-                                                      uint32_t n) {
-    for (uint64_t x = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; x <= n; x += (uint64_t)gridDim.x * blockDim.x)
-        off[x] += coff[x];
-}
-
-// 5a. items per chunk entry: the shorter list's length for the entry (u, v) with u < v (each
-// chunk edge once), 0 for the other direction
-__global__ void __launch_bounds__(kThreads) k_inc_lens(const uint64_t* __restrict__ ck, uint64_t N2,
-                                                       const uint32_t* __restrict__ off, uint64_t* __restrict__ len) {
-    for (uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; p < N2; p += (uint64_t)gridDim.x * blockDim.x) {
-        const uint64_t k = ck[p];
+// 4. end[p] = items of the chunk entries 0 .. p: the shorter list's length for the entry (u, v) with
+// u < v (each chunk edge once), 0 for the other direction
+constexpr uint32_t kItems = 8, kItemTile = kThreads * kItems;
+static_assert(kThreads == scan::kScanThreads, "workgroups of the scans");
+__global__ void __launch_bounds__(kThreads) k_inc_items(const uint64_t* __restrict__ ck, uint64_t N2,
+                                                        const uint32_t* __restrict__ noff, uint64_t* __restrict__ end,
+                                                        uint64_t* __restrict__ total, scan::Look L) {
+    const uint32_t t = scan::look_ticket(L);
+    const uint64_t b0 = (uint64_t)t * kItemTile + (uint64_t)threadIdx.x * kItems;
+    uint32_t len[kItems];
+    uint64_t sum = 0;
+#pragma unroll
+    for (uint32_t r = 0; r < kItems; ++r) {
+        const uint64_t k = b0 + r < N2 ? ck[b0 + r] : 0ull;
         const uint32_t u = hi32(k), v = lo32(k);
-        uint64_t l = 0;
+        len[r] = 0;
         if (u < v) {
-            const uint32_t du = off[u + 1] - off[u], dv = off[v + 1] - off[v];
-            l = du < dv ? du : dv;
+            const uint32_t du = noff[u + 1] - noff[u], dv = noff[v + 1] - noff[v];
+            len[r] = du < dv ? du : dv;
         }
-        len[p] = l;
+        sum += len[r];
     }
+    uint64_t tot;
+    uint64_t run = scan::block_excl_scan<uint64_t>(sum, tot);
+    run += scan::look_back<uint64_t>(L, t, tot);
+#pragma unroll
+    for (uint32_t r = 0; r < kItems; ++r) {
+        run += len[r];
+        if (b0 + r < N2) end[b0 + r] = run;
+    }
+    if (t == gridDim.x - 1 && threadIdx.x == kThreads - 1) *total = run;
 }
 
 // first p in [lo, hi) with end[p] > i (end ascending)
@@ -156,12 +202,26 @@ __device__ __forceinline__ uint64_t upper_item(const uint64_t* __restrict__ end,
     return lo;
 }
 
-// 5b. the count: item i belongs to the chunk entry p with end[p - 1] <= i < end[p].  A workgroup
-// takes kRun consecutive items; the slice of `end` they fall in is staged in LDS when it is
+// the same by a wavefront: 64 places tried at a time
+__device__ __forceinline__ uint64_t wave_upper_item(const uint64_t* __restrict__ end, uint64_t lo, uint64_t hi,
+                                                    uint64_t i) {
+    const uint32_t lane = threadIdx.x & 63;
+    while (hi - lo > 64) {
+        const uint64_t step = (hi - lo + 63) / 64, q = lo + (lane + 1) * step - 1;
+        lo += (uint64_t)__popcll(__ballot(q < hi && end[q] <= i)) * step;
+        hi = hi < lo + step ? hi : lo + step;
+    }
+    return lo + (uint64_t)__popcll(__ballot(lo + lane < hi && end[lo + lane] <= i));
+}
+
+// 5. the count: item i belongs to the chunk entry p with end[p - 1] <= i < end[p].  A workgroup
+// takes a run of consecutive items; the slice of `end` they fall in is staged in LDS when it is
 // short enough (entries without items, the reverse direction of each edge, also sit in it),
 // so that each item finds its entry there.
-constexpr uint32_t kRun = 4096;    // items per workgroup run (16 per thread)
-constexpr uint32_t kStage = 4096;  // entries of `end` staged per run, at most
+constexpr uint32_t kRun = 4096;    // items per workgroup run, at most (16 per thread)
+constexpr uint32_t kRunMin = 256;  // and at least: fewer items are spread over the grid (90k items of a
+                                   // 1,000-edge chunk in runs of 4096 are 22 workgroups: 91 us, now 17)
+constexpr uint32_t kStage = 2048;  // entries of `end` staged per run, at most
 __global__ void __launch_bounds__(kThreads) k_inc_count(IncCount a) {
     __shared__ unsigned int hist[kHist];
     __shared__ uint64_t s_end[kStage];
@@ -172,8 +232,10 @@ __global__ void __launch_bounds__(kThreads) k_inc_count(IncCount a) {
     // items counted into the histogram since its last flush: each item adds at most one to a
     // processor's counter, so flushing once this reaches 2^31 keeps every counter below 2^32
     uint64_t since = 0;
-    for (uint64_t i0 = (uint64_t)blockIdx.x * kRun; i0 < total; i0 += (uint64_t)gridDim.x * kRun) {
-        const uint64_t i1 = (i0 + kRun) < total ? (i0 + kRun) : total;
+    uint64_t run = (total / gridDim.x + kThreads) / kThreads * kThreads;
+    run = run < kRunMin ? kRunMin : run > kRun ? kRun : run;
+    for (uint64_t i0 = (uint64_t)blockIdx.x * run; i0 < total; i0 += (uint64_t)gridDim.x * run) {
+        const uint64_t i1 = (i0 + run) < total ? (i0 + run) : total;
         if (use_hist && since + (i1 - i0) > (1ull << 31)) {  // uniform over the workgroup
             __syncthreads();
             for (uint32_t i = threadIdx.x; i < a.c; i += blockDim.x) {
@@ -184,9 +246,13 @@ __global__ void __launch_bounds__(kThreads) k_inc_count(IncCount a) {
         }
         since += i1 - i0;
         __syncthreads();  // the previous run's readers of s_end are done (and the flush's)
-        if (threadIdx.x == 0) {
-            s_lo = upper_item(a.end, 0, a.N2, i0);
-            s_hi = upper_item(a.end, s_lo, a.N2, i1 - 1) + 1;  // entries [lo, hi) hold the run
+        if (threadIdx.x < 128) {  // entries [lo, hi) hold the run
+            const bool up = threadIdx.x >= 64;
+            const uint64_t at = wave_upper_item(a.end, 0, a.N2, up ? i1 - 1 : i0);
+            if ((threadIdx.x & 63) == 0) {
+                if (up) s_hi = at + 1;
+                else s_lo = at;
+            }
         }
         __syncthreads();
         const uint64_t plo = s_lo, phi = s_hi;
@@ -259,223 +325,174 @@ uint32_t grid_of(uint64_t items, uint32_t cap) {
     return b ? (uint32_t)b : 1u;
 }
 
-// ---- scans: a tile of SC_TILE items per block (256 threads x 16), the tiles' sums scanned by one
-// block, then each tile scanned again from its base
-constexpr uint32_t SC_ITEMS = 16;
-constexpr uint32_t SC_TILE = kThreads * SC_ITEMS;
+// ---- stable LSD radix sort of (key, time) pairs.  The digits are cut from the key's two ids put
+// together (x << id_bits | y), at most kDigit bits each and as even as they come, so that ids of 17
+// bits take four passes.  A workgroup takes a tile of RS_TILE pairs, each wavefront a contiguous part
+// of it, held in registers; a pass counts the digits per tile, scans the counts digit-major (all
+// tiles' 0s, then all tiles' 1s, ...), and scatters each tile stably: a wavefront ranks its lanes
+// among the lanes of the same digit (a ballot per bit) behind its running count of the digit, and the
+// wavefronts' counts, summed from the tile's base, place them.  The first pass's counts come from the
+// kernel that makes the keys.  Short of pairs in flight at these sizes (a chunk of 200k edges is 98
+// tiles), so the workgroups are large: 16 wavefronts to a tile and wider digits, with one launch per
+// scan, take 97 us for that chunk with 17-bit ids, where four wavefronts, digits of 8 bits and three
+// launches per scan took 250.
+constexpr uint32_t RS_THREADS = 1024, RS_WAVES = RS_THREADS / 64;
+constexpr uint32_t RS_TILE = 4096, RS_WAVE = RS_TILE / RS_WAVES, RS_ITEMS = RS_WAVE / 64;
+constexpr uint32_t kDigit = 9;
+constexpr uint32_t kScanItems = 16, kScanTile = kThreads * kScanItems;
 
-template <typename T>
-__device__ T block_excl_scan(T v, T& total) {  // 256 threads
-    __shared__ T ws[kThreads / 64];
-    const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    T inc = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const T o = __shfl_up(inc, d, 64);
-        if ((int)lane >= d) inc += o;
-    }
-    if (lane == 63) ws[w] = inc;
-    __syncthreads();
-    T base = 0, tot = 0;
-#pragma unroll
-    for (uint32_t i = 0; i < kThreads / 64; ++i) {
-        if (i < w) base += ws[i];
-        tot += ws[i];
-    }
-    __syncthreads();
-    total = tot;
-    return base + inc - v;
+struct Digit {
+    uint32_t id_bits, shift, bits;
+};
+__device__ __forceinline__ uint32_t digit_of(const Digit& d, uint64_t k) {
+    return (uint32_t)((((uint64_t)hi32(k) << d.id_bits) | lo32(k)) >> d.shift) & ((1u << d.bits) - 1u);
 }
 
-template <typename T>
-__global__ void __launch_bounds__(kThreads) k_scan_sums(const T* __restrict__ in, uint64_t N, T* __restrict__ part) {
-    const uint64_t b0 = (uint64_t)blockIdx.x * SC_TILE;
-    T s = 0;
-    for (uint32_t r = 0; r < SC_ITEMS; ++r) {
-        const uint64_t i = b0 + (uint64_t)r * kThreads + threadIdx.x;
-        if (i < N) s += in[i];
-    }
-    T tot;
-    (void)block_excl_scan<T>(s, tot);
-    if (threadIdx.x == 0) part[blockIdx.x] = tot;
-}
-
-// exclusive scan of the tiles' sums in place (one block)
-template <typename T>
-__global__ void __launch_bounds__(kThreads) k_scan_parts(T* part, uint32_t nparts) {
-    __shared__ T carry;
-    if (threadIdx.x == 0) carry = 0;
+// 1b. chunk edges -> keys of both directions and times, a tile of RS_TILE keys per workgroup
+__global__ void __launch_bounds__(RS_THREADS) k_inc_keys(const uint2* __restrict__ edges, IncChunk a, Digit dg,
+                                                         uint32_t* __restrict__ hist) {
+    __shared__ uint32_t h[1u << kDigit];
+    for (uint32_t i = threadIdx.x; i < 1u << kDigit; i += RS_THREADS) h[i] = 0;
+    for (uint32_t k = blockIdx.x * RS_THREADS + threadIdx.x; k < a.look_words; k += gridDim.x * RS_THREADS)
+        a.look[k] = 0ull;
     __syncthreads();
-    for (uint32_t b = 0; b < nparts; b += kThreads) {
-        const uint32_t i = b + threadIdx.x;
-        const T v = i < nparts ? part[i] : 0;
-        T tot;
-        const T ex = block_excl_scan<T>(v, tot);
-        const T c = carry;
-        if (i < nparts) part[i] = c + ex;
-        __syncthreads();
-        if (threadIdx.x == 0) carry = c + tot;
-        __syncthreads();
+    uint32_t f = 0;
+#pragma unroll
+    for (uint32_t r = 0; r < RS_TILE / 2; r += RS_THREADS) {
+        const uint64_t i = (uint64_t)blockIdx.x * (RS_TILE / 2) + r + threadIdx.x;
+        if (i < a.W) {
+            uint2 e = edges[i];
+            a.eall[i] = e;
+            f |= edge_flags(e, a.n);
+            const uint64_t k0 = edge_key(e, false), k1 = edge_key(e, true);
+            *(ulonglong2*)(a.ckey + 2 * i) = make_ulonglong2(k0, k1);
+            *(uint2*)(a.ctim + 2 * i) = make_uint2(a.T + (uint32_t)i, a.T + (uint32_t)i);
+            atomicAdd(&h[digit_of(dg, k0)], 1u);
+            atomicAdd(&h[digit_of(dg, k1)], 1u);
+        }
     }
+    if (f) atomicOr(a.flags, f);
+    __syncthreads();
+    for (uint32_t d = threadIdx.x; d < 1u << dg.bits; d += RS_THREADS) hist[(uint64_t)d * gridDim.x + blockIdx.x] = h[d];
 }
 
-// out[i] = sum of in[0..i] (INCL) or in[0..i) (exclusive), each thread 16 consecutive items
-template <typename T, bool INCL>
-__global__ void __launch_bounds__(kThreads) k_scan_items(const T* __restrict__ in, uint64_t N,
-                                                         const T* __restrict__ part, T* __restrict__ out) {
-    const uint64_t b0 = (uint64_t)blockIdx.x * SC_TILE + (uint64_t)threadIdx.x * SC_ITEMS;
-    T v[SC_ITEMS];
-    T s = 0;
+__global__ void __launch_bounds__(RS_THREADS) k_rs_hist(const uint64_t* __restrict__ keys, uint64_t N, Digit dg,
+                                                        uint32_t* __restrict__ hist) {
+    __shared__ uint32_t h[1u << kDigit];
+    for (uint32_t i = threadIdx.x; i < 1u << kDigit; i += RS_THREADS) h[i] = 0;
+    __syncthreads();
+    const uint64_t b0 = (uint64_t)blockIdx.x * RS_TILE;
 #pragma unroll
-    for (uint32_t r = 0; r < SC_ITEMS; ++r) {
-        const uint64_t i = b0 + r;
-        v[r] = i < N ? in[i] : 0;
+    for (uint32_t r = 0; r < RS_TILE; r += RS_THREADS) {
+        const uint64_t i = b0 + r + threadIdx.x;
+        if (i < N) atomicAdd(&h[digit_of(dg, keys[i])], 1u);
+    }
+    __syncthreads();
+    for (uint32_t d = threadIdx.x; d < 1u << dg.bits; d += RS_THREADS) hist[(uint64_t)d * gridDim.x + blockIdx.x] = h[d];
+}
+
+// exclusive scan of c[0, N) in place
+__global__ void __launch_bounds__(kThreads) k_rs_scan(uint32_t* c, uint32_t N, scan::Look L) {
+    const uint32_t t = scan::look_ticket(L);
+    const uint32_t b0 = t * kScanTile + threadIdx.x * kScanItems;
+    uint32_t v[kScanItems], s = 0;
+#pragma unroll
+    for (uint32_t r = 0; r < kScanItems; ++r) {
+        v[r] = b0 + r < N ? c[b0 + r] : 0u;
         s += v[r];
     }
-    T tot;
-    T run = block_excl_scan<T>(s, tot) + part[blockIdx.x];
+    uint32_t tot;
+    uint32_t run = scan::block_excl_scan<uint32_t>(s, tot);
+    run += scan::look_back<uint32_t>(L, t, tot);
 #pragma unroll
-    for (uint32_t r = 0; r < SC_ITEMS; ++r) {
-        const uint64_t i = b0 + r;
-        if (INCL) run += v[r];
-        if (i < N) out[i] = run;
-        if (!INCL) run += v[r];
+    for (uint32_t r = 0; r < kScanItems; ++r) {
+        if (b0 + r < N) c[b0 + r] = run;
+        run += v[r];
     }
 }
 
-template <typename T, bool INCL>
-hipError_t scan_items(const T* in, uint64_t N, T* part, T* out, hipStream_t s) {
-    const uint64_t nb = (N + SC_TILE - 1) / SC_TILE;
-    if (nb == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_scan_sums<T>, dim3((uint32_t)nb), dim3(kThreads), 0, s, in, N, part);
-    hipLaunchKernelGGL(k_scan_parts<T>, dim3(1), dim3(kThreads), 0, s, part, (uint32_t)nb);
-    hipLaunchKernelGGL((k_scan_items<T, INCL>), dim3((uint32_t)nb), dim3(kThreads), 0, s, in, N, part, out);
-    return hipGetLastError();
-}
-
-// ---- stable LSD radix sort of (key, time) pairs: one 8-bit digit per pass.  A block takes a
-// tile of RS_TILE pairs, each of its four wavefronts a contiguous quarter; the pass counts the
-// digits per tile, scans the counts digit-major (all tiles' 0s, then all tiles' 1s, ...), and
-// scatters each tile stably: a wavefront ranks its lanes among the lanes of the same digit
-// (eight ballots) and keeps a running base per digit, seeded from the tile's base plus the
-// counts of the wavefronts before it.
-constexpr uint32_t RS_TILE = 4096;
-constexpr uint32_t RS_WAVE = RS_TILE / (kThreads / 64);
-
-__global__ void __launch_bounds__(kThreads) k_rs_hist(const uint64_t* __restrict__ keys, uint64_t N, uint32_t shift,
-                                                      uint32_t nb, uint32_t* __restrict__ hist) {
-    __shared__ uint32_t h[256];
-    h[threadIdx.x] = 0;
-    __syncthreads();
-    const uint64_t b0 = (uint64_t)blockIdx.x * RS_TILE, b1 = (b0 + RS_TILE) < N ? (b0 + RS_TILE) : N;
-    for (uint64_t i = b0 + threadIdx.x; i < b1; i += kThreads) atomicAdd(&h[(uint32_t)(keys[i] >> shift) & 255u], 1u);
-    __syncthreads();
-    hist[(uint64_t)threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
-}
-
-__global__ void __launch_bounds__(kThreads) k_rs_scatter(const uint64_t* __restrict__ kin, const uint32_t* __restrict__ vin,
-                                                         uint64_t N, uint32_t shift, uint32_t nb,
-                                                         const uint32_t* __restrict__ offs, uint64_t* __restrict__ kout,
-                                                         uint32_t* __restrict__ vout) {
-    __shared__ uint32_t wc[kThreads / 64][256];  // per wavefront: digit counts, then running bases
+__global__ void __launch_bounds__(RS_THREADS) k_rs_scatter(const uint64_t* __restrict__ kin,
+                                                           const uint32_t* __restrict__ vin, uint64_t N, Digit dg,
+                                                           const uint32_t* __restrict__ base,
+                                                           uint64_t* __restrict__ kout, uint32_t* __restrict__ vout) {
+    __shared__ uint32_t wc[RS_WAVES][1u << kDigit];  // per wavefront: digit counts, then bases
     const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    for (uint32_t i = threadIdx.x; i < (kThreads / 64) * 256; i += kThreads) (&wc[0][0])[i] = 0;
-    __syncthreads();
     const uint64_t t0 = (uint64_t)blockIdx.x * RS_TILE + (uint64_t)w * RS_WAVE;
-    const uint64_t t1 = (t0 + RS_WAVE) < N ? (t0 + RS_WAVE) : N;
-    for (uint64_t c0 = t0; c0 < t1; c0 += 64) {
-        const uint64_t i = c0 + lane;
-        if (i < t1) atomicAdd(&wc[w][(uint32_t)(kin[i] >> shift) & 255u], 1u);
+    uint64_t k[RS_ITEMS];
+    uint32_t t[RS_ITEMS], at[RS_ITEMS];
+#pragma unroll
+    for (uint32_t r = 0; r < RS_ITEMS; ++r) {
+        const uint64_t i = t0 + r * 64 + lane;
+        k[r] = i < N ? kin[i] : 0ull;
+        t[r] = i < N ? vin[i] : 0u;
+    }
+    for (uint32_t i = threadIdx.x; i < RS_WAVES << kDigit; i += RS_THREADS) (&wc[0][0])[i] = 0;
+    __syncthreads();
+    const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
+#pragma unroll
+    for (uint32_t r = 0; r < RS_ITEMS; ++r) {
+        const bool valid = t0 + r * 64 + lane < N;
+        const uint32_t dig = digit_of(dg, k[r]);
+        uint64_t peers = __ballot(valid);
+        for (uint32_t bit = 0; bit < dg.bits; ++bit) {
+            const bool one = (dig >> bit) & 1u;
+            const uint64_t bb = __ballot(valid && one);
+            peers &= one ? bb : ~bb;
+        }
+        at[r] = wc[w][dig] + (uint32_t)__popcll(peers & below);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // every lane has read its digit's count
+        __builtin_amdgcn_wave_barrier();
+        if (valid && (int)lane == 63 - __clzll(peers)) wc[w][dig] += (uint32_t)__popcll(peers);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
-    {  // thread d: the bases of digit d for the four wavefronts of this tile
-        const uint32_t d = threadIdx.x;
-        uint32_t run = offs[(uint64_t)d * nb + blockIdx.x];
-        for (uint32_t v = 0; v < kThreads / 64; ++v) {
+    for (uint32_t d = threadIdx.x; d < 1u << dg.bits; d += RS_THREADS) {
+        uint32_t run = base[(uint64_t)d * gridDim.x + blockIdx.x];
+#pragma unroll
+        for (uint32_t v = 0; v < RS_WAVES; ++v) {
             const uint32_t c = wc[v][d];
             wc[v][d] = run;
             run += c;
         }
     }
     __syncthreads();
-    const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
-    for (uint64_t c0 = t0; c0 < t1; c0 += 64) {
-        const uint64_t i = c0 + lane;
-        const bool valid = i < t1;
-        const uint64_t k = valid ? kin[i] : 0ull;
-        const uint32_t t = valid ? vin[i] : 0u;
-        const uint32_t dig = (uint32_t)(k >> shift) & 255u;
-        uint64_t peers = __ballot(valid);
 #pragma unroll
-        for (int bit = 0; bit < 8; ++bit) {
-            const uint64_t bb = __ballot(valid && ((dig >> bit) & 1u));
-            peers &= ((dig >> bit) & 1u) ? bb : ~bb;
+    for (uint32_t r = 0; r < RS_ITEMS; ++r)
+        if (t0 + r * 64 + lane < N) {
+            const uint32_t q = wc[w][digit_of(dg, k[r])] + at[r];
+            kout[q] = k[r];
+            vout[q] = t[r];
         }
-        const uint32_t pos = wc[w][dig] + (uint32_t)__popcll(peers & below);
-        if (valid) {
-            kout[pos] = k;
-            vout[pos] = t;
-            // the highest lane of the digit advances its base (after every lane has read it)
-            if ((int)lane == 63 - __clzll(peers)) wc[w][dig] += (uint32_t)__popcll(peers);
-        }
-    }
 }
 
-__global__ void k_copy_pairs(const uint64_t* __restrict__ ks, const uint32_t* __restrict__ vs, uint64_t N,
-                             uint64_t* __restrict__ kd, uint32_t* __restrict__ vd) {
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (uint64_t)gridDim.x * blockDim.x) {
-        kd[i] = ks[i];
-        vd[i] = vs[i];
-    }
-}
-
-// temporary storage of the sort and the scans: the digit counts and their scan, then the scans'
-// tile sums
+// temporary storage of an append: the digit counts, then the scans' words (one scan per digit and the
+// items' scan, which comes first), which the append's first kernel clears
 struct SortTemp {
-    size_t hist, offs, part, total;
+    size_t hist, look, total;
+    uint32_t nb, digit_words, item_words;  // tiles; words of a digit's scan and of the items' scan
 };
 SortTemp sort_temp(uint64_t N) {
     SortTemp T;
-    const uint64_t nb = (N + RS_TILE - 1) / RS_TILE;
-    const uint64_t nh = 256 * (nb ? nb : 1);
-    const uint64_t parts = (nh + SC_TILE - 1) / SC_TILE + (N + SC_TILE - 1) / SC_TILE + 2;
+    T.nb = (uint32_t)((N + RS_TILE - 1) / RS_TILE);
+    if (T.nb == 0) T.nb = 1;
+    const uint64_t nh = (uint64_t)T.nb << kDigit;
+    T.digit_words = 1 + (uint32_t)((nh + kScanTile - 1) / kScanTile);
+    T.item_words = 1 + (uint32_t)((N + kItemTile - 1) / kItemTile);
+    constexpr uint32_t passes = (2 * 29 + kDigit - 1) / kDigit;  // ids below 2^29
     size_t p = 0;
     T.hist = p; p = (p + 4 * nh + 255) & ~(size_t)255;
-    T.offs = p; p = (p + 4 * (nh + 1) + 255) & ~(size_t)255;
-    T.part = p; p = (p + 8 * parts + 255) & ~(size_t)255;
+    T.look = p; p = (p + 8 * ((uint64_t)T.item_words + passes * T.digit_words) + 255) & ~(size_t)255;
     T.total = p;
     return T;
 }
+scan::Look look_at(unsigned long long* words) { return scan::Look{(uint32_t*)words, words + 1}; }
 
-// sorts (ka, ta) by the key bits below end_bit that can be set (ids below 2^(end_bit - 32) on
-// both halves), the result in (kb, tb); (ka, ta) is overwritten
-hipError_t radix_sort_keys(void* temp, uint64_t N, uint32_t end_bit, uint64_t* ka, uint32_t* ta, uint64_t* kb,
-                           uint32_t* tb, hipStream_t s) {
-    if (N == 0) return hipSuccess;
-    const SortTemp L = sort_temp(N);
-    uint32_t* hist = (uint32_t*)((uint8_t*)temp + L.hist);
-    uint32_t* offs = (uint32_t*)((uint8_t*)temp + L.offs);
-    uint32_t* part = (uint32_t*)((uint8_t*)temp + L.part);
-    const uint32_t nb = (uint32_t)((N + RS_TILE - 1) / RS_TILE);
-    const uint32_t id_bits = end_bit - 32;
-    uint64_t *src_k = ka, *dst_k = kb;
-    uint32_t *src_t = ta, *dst_t = tb;
-    for (uint32_t half = 0; half < 2; ++half) {  // y (bits 0..), then x (bits 32..)
-        for (uint32_t b = 0; b < id_bits; b += 8) {
-            const uint32_t shift = 32 * half + b;
-            hipLaunchKernelGGL(k_rs_hist, dim3(nb), dim3(kThreads), 0, s, src_k, N, shift, nb, hist);
-            hipError_t e = scan_items<uint32_t, false>(hist, (uint64_t)256 * nb, part, offs, s);
-            if (e != hipSuccess) return e;
-            hipLaunchKernelGGL(k_rs_scatter, dim3(nb), dim3(kThreads), 0, s, src_k, src_t, N, shift, nb, offs, dst_k,
-                               dst_t);
-            uint64_t* tk = src_k; src_k = dst_k; dst_k = tk;
-            uint32_t* tt = src_t; src_t = dst_t; dst_t = tt;
-        }
-    }
-    if (src_k != kb)
-        hipLaunchKernelGGL(k_copy_pairs, dim3(grid_of(N, 8192)), dim3(kThreads), 0, s, src_k, src_t, N, kb, tb);
-    return hipGetLastError();
-}
+// Chunks of at most this many edges are sorted by k_inc_rank, whose compares grow with the square of
+// the chunk (up to here it has a workgroup per CU at most), while the radix sort's launches hardly grow.
+// A whole append to 100k nodes by either: 1,000 edges 68 and 124 us, 4,000 95 and 149, 8,000 125 and
+// 155, 12,000 238 and 158; to 3,000 nodes (three digits instead of four) 8,000 edges 131 and 139.
+constexpr uint64_t kRankEdges = 8192;
 
 }  // namespace
 
@@ -492,40 +509,63 @@ hipError_t rept_inc_zero64(void* p, uint64_t words, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t rept_inc_prepare(const IncState& st, const uint32_t* edges, uint64_t W, hipStream_t s) {
+hipError_t rept_inc_prepare(IncState& st, const uint32_t* edges, uint64_t W, uint32_t* eall, hipStream_t s) {
     (void)hipGetLastError();
-    const uint64_t N2 = 2 * W;
-    hipLaunchKernelGGL(k_inc_zero64, dim3(1), dim3(64), 0, s, (uint64_t*)st.flags, (uint64_t)1);
-    hipLaunchKernelGGL(k_inc_keys, dim3(grid_of(W, 8192)), dim3(kThreads), 0, s, (const uint2*)edges, W, st.n,
-                       (uint32_t)st.T, st.ckey_a, st.ctim_a, st.flags);
-    hipError_t e = radix_sort_keys(st.temp, N2, st.end_bit, st.ckey_a, st.ctim_a, st.ckey_b, st.ctim_b, s);
-    if (e != hipSuccess) return e;
-    const uint64_t* akey = st.key[st.cur];
-    hipLaunchKernelGGL(k_inc_check, dim3(grid_of(N2, 8192)), dim3(kThreads), 0, s, st.ckey_b, N2, akey, st.off,
-                       st.flags);
-    hipLaunchKernelGGL(k_inc_coff, dim3(grid_of((uint64_t)st.n + 1, 8192)), dim3(kThreads), 0, s, st.ckey_b, N2,
-                       st.n, st.coff);
+    const uint64_t N2 = 2 * W, N = 2 * st.T;
+    const SortTemp L = sort_temp(N2);
+    uint32_t* hist = (uint32_t*)((uint8_t*)st.temp + L.hist);
+    unsigned long long* look = (unsigned long long*)((uint8_t*)st.temp + L.look);
+    if (!st.flags_clear)
+        hipLaunchKernelGGL(k_inc_zero64, dim3(1), dim3(64), 0, s, (uint64_t*)st.flags, (uint64_t)1);
+    st.flags_clear = false;  // until the host has read them as zero
+    IncChunk a{W, st.n, (uint32_t)st.T, st.ckey_b, st.ctim_b, (uint2*)eall, st.flags, look, L.item_words};
+    if (W <= kRankEdges) {
+        hipLaunchKernelGGL(k_inc_rank, dim3((uint32_t)((N2 + 63) / 64)), dim3(kRankThreads), 0, s, (const uint2*)edges, a);
+    } else {
+        const uint32_t id_bits = st.end_bit - 32, passes = (2 * id_bits + kDigit - 1) / kDigit;
+        uint64_t *src_k = st.ckey_b, *dst_k = st.ckey_a;  // the last pass ends in b
+        uint32_t *src_t = st.ctim_b, *dst_t = st.ctim_a;
+        if (passes & 1u) {
+            src_k = st.ckey_a; dst_k = st.ckey_b;
+            src_t = st.ctim_a; dst_t = st.ctim_b;
+        }
+        a.ckey = src_k;
+        a.ctim = src_t;
+        a.look_words = L.item_words + passes * L.digit_words;
+        Digit dg{id_bits, 0, 0};
+        for (uint32_t p = 0; p < passes; ++p) {
+            dg.shift += dg.bits;
+            dg.bits = (2 * id_bits - dg.shift + passes - p - 1) / (passes - p);
+            if (p == 0)
+                hipLaunchKernelGGL(k_inc_keys, dim3(L.nb), dim3(RS_THREADS), 0, s, (const uint2*)edges, a, dg, hist);
+            else
+                hipLaunchKernelGGL(k_rs_hist, dim3(L.nb), dim3(RS_THREADS), 0, s, src_k, N2, dg, hist);
+            const uint32_t nh = L.nb << dg.bits;
+            hipLaunchKernelGGL(k_rs_scan, dim3((nh + kScanTile - 1) / kScanTile), dim3(kThreads), 0, s, hist, nh,
+                               look_at(look + L.item_words + p * L.digit_words));
+            hipLaunchKernelGGL(k_rs_scatter, dim3(L.nb), dim3(RS_THREADS), 0, s, src_k, src_t, N2, dg, hist, dst_k,
+                               dst_t);
+            uint64_t* tk = src_k; src_k = dst_k; dst_k = tk;
+            uint32_t* tt = src_t; src_t = dst_t; dst_t = tt;
+        }
+    }
+    const int nxt = st.cur ^ 1;
+    hipLaunchKernelGGL(k_inc_noff, dim3(grid_of((uint64_t)st.n + 1, 8192)), dim3(kThreads), 0, s, st.ckey_b, N2, st.n,
+                       st.off, st.noff);
+    hipLaunchKernelGGL(k_inc_merge, dim3(grid_of(N + N2, 8192)), dim3(kThreads), 0, s, st.key[st.cur], st.tim[st.cur],
+                       N, st.ckey_b, st.ctim_b, N2, st.off, st.noff, st.key[nxt], st.tim[nxt], st.flags);
+    hipLaunchKernelGGL(k_inc_items, dim3((uint32_t)((N2 + kItemTile - 1) / kItemTile)), dim3(kThreads), 0, s,
+                       st.ckey_b, N2, st.noff, st.end, (uint64_t*)st.flags + 1, look_at(look));
     return hipGetLastError();
 }
 
-hipError_t rept_inc_merge(IncState& st, uint64_t W, hipStream_t s) {
-    (void)hipGetLastError();
-    const uint64_t N2 = 2 * W, N = 2 * st.T;
-    const int nxt = st.cur ^ 1;
-    hipLaunchKernelGGL(k_inc_merge_old, dim3(grid_of(N, 8192)), dim3(kThreads), 0, s, st.key[st.cur], st.tim[st.cur],
-                       N, st.off, st.coff, st.ckey_b, st.key[nxt], st.tim[nxt]);
-    hipLaunchKernelGGL(k_inc_merge_new, dim3(grid_of(N2, 8192)), dim3(kThreads), 0, s, st.ckey_b, st.ctim_b, N2,
-                       st.off, st.key[st.cur], st.key[nxt], st.tim[nxt]);
-    hipLaunchKernelGGL(k_inc_off, dim3(grid_of((uint64_t)st.n + 1, 8192)), dim3(kThreads), 0, s, st.off, st.coff,
-                       st.n);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    st.cur = nxt;
+void rept_inc_accept(IncState& st, uint64_t W) {
+    uint32_t* o = st.off;
+    st.off = st.noff;
+    st.noff = o;
+    st.cur ^= 1;
     st.T += W;
-    // the chunk's work items: one per entry of the shorter endpoint list of each chunk edge
-    uint64_t* len = st.ckey_a;  // free after the sort
-    hipLaunchKernelGGL(k_inc_lens, dim3(grid_of(N2, 8192)), dim3(kThreads), 0, s, st.ckey_b, N2, st.off, len);
-    return scan_items<uint64_t, true>(len, N2, (uint64_t*)((uint8_t*)st.temp + sort_temp(N2).part), st.end, s);
+    st.flags_clear = true;
 }
 
 hipError_t rept_inc_count(const IncState& st, uint64_t W, const IncCount& base, hipStream_t s) {

@@ -125,3 +125,48 @@ def test_invalid_chunks_leave_state_unchanged(cuda):
     inc.append(rept.to_device_edges(e[750:750], cuda))  # an empty chunk changes nothing
     _check(inc, e[:750], 100, p)
     inc.close()
+
+
+@pytest.mark.parametrize("n,head,chunks", [
+    (300, 8192, [1, 31, 32, 33, 64, 2047]),      # the pairwise sort: a workgroup's 32 edges, less and more
+    (300, 8193, [8192, 8193, 4096, 1]),          # the largest pairwise sort, the smallest radix sort
+    (4096, 8193, [10240, 10239, 12289]),         # 12-bit ids (three digits); tiles of 2,048 edges
+    (70000, 30001, [9000, 8192]),                # 17-bit ids (four digits), more nodes than edges
+    ((1 << 22) + 1, 8193, [20000]),              # 23-bit ids (six digits)
+])
+def test_chunk_sort_sizes(cuda, n, head, chunks):
+    """Chunks at the edges of the sorts' sizes; after each, a repeat of one of its pairs (reversed) and of
+    an earlier one is refused at a size of either sort."""
+    from paper_1811_09136_amd import rept
+    E = head + sum(chunks)
+    e = synth.er(min(n, 70000), E, 5, 6)
+    if n > 70000:
+        e = (e * np.uint32(59)).astype(np.uint32)
+    p = rept.Params(2, 5, 11)
+    inc = rept.IncrementalStream(n, E + 10000, 20000 if head < 20000 else head, p, cuda, policy="per_edge")
+    at = 0
+    for w in [head] + chunks:
+        _say(f"chunk sort n={n} at={at} W={w}")
+        inc.append(rept.to_device_edges(e[at:at + w], cuda))
+        at += w
+        for k in (2, 8194):
+            for pair in (e[at - 1], e[0][::-1]):
+                bad = np.vstack([_fresh(n, k, e), [pair]]).astype(np.uint32)
+                with pytest.raises(rept.ReptError) as ei:
+                    inc.append(rept.to_device_edges(bad, cuda))
+                assert ei.value.code == rept.REPT_EDUP
+    _check(inc, e[:at], n, p)
+    inc.close()
+
+
+def _fresh(n, k, e):
+    """k pairs that are not in the stream e."""
+    if n == 300:
+        used = {(min(u, v), max(u, v)) for u, v in e.tolist()}
+        out = [(u, v) for u in range(n) for v in range(u + 1, n) if (u, v) not in used]
+        return np.array(out[:k], np.uint32)
+    used = set((np.minimum(e[:, 0], e[:, 1]).astype(np.int64) * n + np.maximum(e[:, 0], e[:, 1])).tolist())
+    u = np.arange(4 * k, dtype=np.int64) % (n - 1)
+    v = u + 1 + np.arange(4 * k, dtype=np.int64) // (n - 1)
+    keep = np.array([x * n + y not in used and y < n for x, y in zip(u, v)])
+    return np.stack([u[keep], v[keep]], 1)[:k].astype(np.uint32)
