@@ -317,9 +317,9 @@ rept_status rept_hash_slots(const rept_params* params, const uint32_t* edges, ui
  *     binary search) per entry of its endpoints' shorter list;
  *   - by a windowed recount: rept_build of the whole stream so far, then rept_count_range over
  *     the chunk's times (a triangle's updates belong to the time of its last edge).
- * By default (REPT_STREAM_AUTO) an append recounts when its work items exceed 10 per edge so far,
- * the ratio of the two costs measured on a 20M-edge power-law stream; rept_stream_set_policy
- * fixes either way.  A recount needs one more stream synchronisation (the build's) and the
+ * By default (REPT_STREAM_AUTO) an append recounts when its work items exceed 24M and 14 per edge so
+ * far, where the two cost about the same on power-law streams of 0.5M to 20M edges;
+ * rept_stream_set_policy fixes either way.  A recount needs one more stream synchronisation (the build's) and the
  * build's regions of the buffer.
  */
 typedef struct rept_stream rept_stream; /* opaque host-side handle */

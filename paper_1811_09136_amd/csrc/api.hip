@@ -95,10 +95,15 @@ bool valid_stream(const rept_stream* s) { return s && s->magic == REPT_STREAM_MA
 
 // The per-edge count of an append costs about one binary search per work item (the chunk's total
 // of min(d_u, d_v) over its edges at the chunk's end); the windowed recount, a build and a count
-// of the whole prefix.  On the 1M/20M power-law stream in ten appends the first took 4.4e-11 s
-// per item and the second 4.5e-10 s per prefix edge, so the recount is taken when the items
-// exceed 10 per prefix edge.
-constexpr uint64_t kRecountItemsPerEdge = 10;
+// of the whole prefix, which costs some 450 us however short the prefix is.  Whole appends by either, on
+// power-law streams (per-edge and recount, us, with the items per prefix edge):
+//   prefix of  0.5M edges:   9.2M items (18)   464 and  694;  45.7M (91)  994 and  773
+//                1M:          33.0M (33)       862 and  869
+//                2M:          26.4M (13)       877 and 1000;  65.8M (33) 1859 and 1111
+//                6M:          79.0M (13)      1654 and 2365; 157.7M (26) 2817 and 2524
+//               20M:         262.0M (13)      6333 and 7751; 523.0M (26) 11535 and 8082
+// so the two are about equal at 24M items and 14 more per prefix edge.
+constexpr uint64_t kRecountItems = 24000000, kRecountItemsPerEdge = 14;
 
 // Count the edges at times [t0, t1) of the stream appended so far by the one-shot path: build
 // the prefix [0, t1) into the handle's reserved regions, then add the window's per-edge updates
@@ -1155,12 +1160,13 @@ rept_status rept_stream_create(uint32_t n, uint64_t capacity, uint64_t max_chunk
     h->gws_bytes = L.gws_bytes;
     h->policy = REPT_STREAM_AUTO;
     const uint32_t cus = rept_num_cus() ? rept_num_cus() : 256;
-    S.count_blocks = 8 * cus;
+    S.count_blocks = 4 * cus;
     IncCount& a = h->base;
     memset(&a, 0, sizeof(a));
     a.global = global;
     a.local = local;
     a.n = n;
+    a.rows = rept_local_rows(params);
     a.m = params->m;
     a.c = params->c;
     a.G = G;
@@ -1211,7 +1217,7 @@ rept_status rept_stream_append(rept_stream* h, const uint32_t* edges, uint64_t n
     if (seen.flags & RF_DUP) return REPT_EDUP;
     rept_inc_accept(h->st, num_edges);
     const bool recount = h->policy == REPT_STREAM_RECOUNT ||
-                         (h->policy == REPT_STREAM_AUTO && seen.items > kRecountItemsPerEdge * h->st.T);
+                         (h->policy == REPT_STREAM_AUTO && seen.items > kRecountItems + kRecountItemsPerEdge * h->st.T);
     if (recount) {
         const rept_status st = recount_window(h, t0, h->st.T, s);
         if (st == REPT_OK) {
@@ -1220,7 +1226,7 @@ rept_status rept_stream_append(rept_stream* h, const uint32_t* edges, uint64_t n
         }
         if (st != REPT_ENOMEM) return st;  // ENOMEM: the prefix outgrew the reserved regions
     }
-    if (rept_inc_count(h->st, num_edges, h->base, s) != hipSuccess) return REPT_EDEVICE;
+    if (rept_inc_count(h->st, num_edges, seen.items, h->base, s) != hipSuccess) return REPT_EDEVICE;
     ++h->n_per_edge;
     return REPT_OK;
 }

@@ -256,7 +256,8 @@ struct IncCount {
     const uint64_t* ck;  // sorted chunk keys
     const uint32_t* ct;  // their times
     const uint64_t* end;
-    uint64_t N2;
+    uint64_t N2, rows;  // rows: of local
+    uint32_t run;       // items a workgroup takes at a time
     int64_t* global;
     int64_t* local;
     uint32_t n, m, c, G;
@@ -272,5 +273,6 @@ hipError_t rept_inc_zero64(void* p, uint64_t words, hipStream_t stream);
 hipError_t rept_inc_prepare(IncState& st, const uint32_t* edges, uint64_t W, uint32_t* eall, hipStream_t stream);
 // the validation word was read as zero: the merged copy becomes the current one (st.T advances)
 void rept_inc_accept(IncState& st, uint64_t W);
-// step 5: count each chunk edge against the edges that arrived before it (after rept_inc_accept)
-hipError_t rept_inc_count(const IncState& st, uint64_t W, const IncCount& base, hipStream_t stream);
+// step 5: count each chunk edge against the edges that arrived before it (after rept_inc_accept;
+// items: the chunk's work items)
+hipError_t rept_inc_count(const IncState& st, uint64_t W, uint64_t items, const IncCount& base, hipStream_t stream);

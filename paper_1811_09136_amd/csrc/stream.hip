@@ -37,6 +37,12 @@ constexpr uint32_t kHist = 1024;  // processors aggregated in LDS by the countin
 __device__ __forceinline__ uint32_t hi32(uint64_t k) { return (uint32_t)(k >> 32); }
 __device__ __forceinline__ uint32_t lo32(uint64_t k) { return (uint32_t)k; }
 
+// orders a wavefront's LDS accesses
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // first index in [lo, hi) with key >= x (keys sorted ascending)
 __device__ __forceinline__ uint64_t lower_bound64(const uint64_t* __restrict__ k, uint64_t lo, uint64_t hi,
                                                   uint64_t x) {
@@ -218,30 +224,120 @@ __device__ __forceinline__ uint64_t wave_upper_item(const uint64_t* __restrict__
 // takes a run of consecutive items; the slice of `end` they fall in is staged in LDS when it is
 // short enough (entries without items, the reverse direction of each edge, also sit in it),
 // so that each item finds its entry there.
-constexpr uint32_t kRun = 4096;    // items per workgroup run, at most (16 per thread)
-constexpr uint32_t kRunMin = 256;  // and at least: fewer items are spread over the grid (90k items of a
-                                   // 1,000-edge chunk in runs of 4096 are 22 workgroups: 91 us, now 17)
-constexpr uint32_t kStage = 2048;  // entries of `end` staged per run, at most
-__global__ void __launch_bounds__(kThreads) k_inc_count(IncCount a) {
+//   The counters' atomics would set the time: all triangles of an edge add to its two nodes, and the
+// third nodes of many edges are the same few large ones, while the memory side takes one atomic per
+// 64-byte line and 12 ns.  So a wavefront, whose items are consecutive, queues its triangles and takes
+// them 64 at a time, adds up each edge's and each first node's, and a workgroup collects its additions
+// in LDS, in a table that keeps the first node to come to an entry (large nodes come first) and is
+// written out at the end; an addition that finds its entry taken goes to memory.  The rest is waiting
+// for the searches: eight wavefronts per SIMD (64 VGPRs, 40 KB of LDS for eight) hide it better than
+// five, a few spilled registers included.  An append of 200k edges to 1.8M (26M items), all of it:
+// 2,890 us with an atomic per addition, 1,353 with the sums, 1,121 with the queues, 903 with 16-bit
+// ends and 64 registers, 877 with searches of the keys' low words alone.
+constexpr uint32_t kRun = 4096;       // items per workgroup run, at most
+constexpr uint32_t kCountThreads = 512;
+constexpr uint32_t kStage = 2048;     // entries of `end` staged per run, at most
+constexpr uint32_t kNodeBits = 11;    // the table of additions has 2^11 entries
+constexpr uint32_t kNoNode = 0xffffffffu;
+
+struct NodeSums {
+    uint32_t key[1u << kNodeBits], sum[1u << kNodeBits];
+};
+// add c to local[k] (kept: k is below kNoNode for every counter)
+__device__ __forceinline__ void node_add(NodeSums& T, bool kept, int64_t* local, uint64_t k, uint32_t c) {
+    if (kept) {
+        const uint32_t key = (uint32_t)k, s = (key * 0x9E3779B1u) >> (32 - kNodeBits);
+        uint32_t have = *(volatile uint32_t*)&T.key[s];
+        if (have == kNoNode) have = atomicCAS(&T.key[s], kNoNode, key);
+        if (have == kNoNode || have == key) {
+            atomicAdd(&T.sum[s], c);
+            return;
+        }
+    }
+    atomicAdd((unsigned long long*)local + k, (unsigned long long)c);
+}
+// the lanes of `heads`' segment that starts at this lane
+__device__ __forceinline__ uint64_t segment(uint64_t heads, uint32_t lane) {
+    const uint64_t later = heads & ~((2ull << lane) - 1ull);
+    return (later ? (later & (0ull - later)) - 1ull : ~0ull) & ~((1ull << lane) - 1ull);
+}
+
+struct Triangles {  // {u, v, w} with last edge (u, v), in the order of the edges
+    uint32_t u[128], v[128], w[128];
+};
+// The first n <= 64 triangles of a wavefront's queue: per group, the processor that stored both {u, w}
+// and {v, w}, if one did, counts the triangle.
+__device__ __forceinline__ void count_triangles(const IncCount& a, const Triangles& q, uint32_t n, uint32_t* hist,
+                                                bool use_hist, NodeSums& sums, bool kept) {
+    const uint32_t lane = threadIdx.x & 63;
+    const bool valid = lane < n;
+    const uint32_t u = valid ? q.u[lane] : kNoNode, v = valid ? q.v[lane] : kNoNode, w = valid ? q.w[lane] : 0u;
+    // (an edge changes where v does, or u)
+    const uint32_t pu = __shfl_up(u, 1, 64), pv = __shfl_up(v, 1, 64);
+    const bool head_u = lane == 0 || pu != u, head_v = head_u || pv != v;
+    const uint64_t seg_u = segment(__ballot(head_u), lane), seg_v = segment(__ballot(head_v), lane);
+    for (uint32_t g = 0; g < a.G; ++g) {
+        const uint64_t* c4 = a.hp + 4 * g;
+        const uint32_t s1 = rept_hash::slot_of(c4, a.m, u, w), s2 = rept_hash::slot_of(c4, a.m, v, w);
+        const uint32_t active = (g + 1 < a.G) ? a.ck_full : a.last_ck;
+        const bool counted = valid && s1 == s2 && s1 < active;
+        const uint32_t proc = g * a.pstride + s1;
+        const uint64_t bal = __ballot(counted);
+        if (!bal) continue;
+        const uint64_t row = (uint64_t)(a.per_proc ? proc : g) * a.n;
+        if (counted) {
+            if (use_hist) atomicAdd(&hist[proc], 1u);
+            else atomicAdd((unsigned long long*)a.global + proc, 1ull);
+            node_add(sums, kept, a.local, row + w, 1u);
+            if (a.per_proc) {  // (a row per lane)
+                node_add(sums, kept, a.local, row + u, 1u);
+                node_add(sums, kept, a.local, row + v, 1u);
+            }
+        }
+        if (!a.per_proc) {
+            const uint32_t cu = (uint32_t)__popcll(bal & seg_u), cv = (uint32_t)__popcll(bal & seg_v);
+            if (head_u && cu) node_add(sums, kept, a.local, row + u, cu);
+            if (head_v && cv) node_add(sums, kept, a.local, row + v, cv);
+        }
+    }
+}
+
+__global__ void __launch_bounds__(kCountThreads, 8) k_inc_count(IncCount a) {
     __shared__ unsigned int hist[kHist];
-    __shared__ uint64_t s_end[kStage];
+    __shared__ uint16_t s_end[kStage];  // from the run's start on; kRun: past the run
+    __shared__ NodeSums sums;
+    __shared__ Triangles queues[kCountThreads / 64];
     __shared__ uint64_t s_lo, s_hi;
-    const bool use_hist = a.c <= kHist;
+    const uint32_t lane = threadIdx.x & 63;
+    Triangles& queue = queues[threadIdx.x >> 6];
+    uint32_t queued = 0;  // (the same in all lanes, below 64 between passes)
+    const bool use_hist = a.c <= kHist, kept = a.rows * a.n < kNoNode;
     for (uint32_t i = threadIdx.x; i < kHist; i += blockDim.x) hist[i] = 0u;
+    for (uint32_t i = threadIdx.x; i < 1u << kNodeBits; i += blockDim.x) {
+        sums.key[i] = kNoNode;
+        sums.sum[i] = 0u;
+    }
     const uint64_t total = a.N2 ? a.end[a.N2 - 1] : 0;
-    // items counted into the histogram since its last flush: each item adds at most one to a
-    // processor's counter, so flushing once this reaches 2^31 keeps every counter below 2^32
-    uint64_t since = 0;
-    uint64_t run = (total / gridDim.x + kThreads) / kThreads * kThreads;
-    run = run < kRunMin ? kRunMin : run > kRun ? kRun : run;
-    for (uint64_t i0 = (uint64_t)blockIdx.x * run; i0 < total; i0 += (uint64_t)gridDim.x * run) {
-        const uint64_t i1 = (i0 + run) < total ? (i0 + run) : total;
-        if (use_hist && since + (i1 - i0) > (1ull << 31)) {  // uniform over the workgroup
-            __syncthreads();
+    const auto flush = [&] {
+        if (use_hist)
             for (uint32_t i = threadIdx.x; i < a.c; i += blockDim.x) {
                 if (hist[i]) atomicAdd((unsigned long long*)a.global + i, (unsigned long long)hist[i]);
                 hist[i] = 0u;
             }
+        for (uint32_t i = threadIdx.x; i < 1u << kNodeBits; i += blockDim.x) {
+            if (sums.sum[i]) atomicAdd((unsigned long long*)a.local + sums.key[i], (unsigned long long)sums.sum[i]);
+            sums.sum[i] = 0u;
+        }
+    };
+    // items taken since the last flush: each adds at most one to a processor's counter and to a
+    // node's (the few queued ones later), so flushing once this reaches 2^31 keeps every LDS
+    // counter below 2^32
+    uint64_t since = 0;
+    for (uint64_t i0 = (uint64_t)blockIdx.x * a.run; i0 < total; i0 += (uint64_t)gridDim.x * a.run) {
+        const uint64_t i1 = (i0 + a.run) < total ? (i0 + a.run) : total;
+        if (since + (i1 - i0) > (1ull << 31)) {  // uniform over the workgroup
+            __syncthreads();
+            flush();
             since = 0;
         }
         since += i1 - i0;
@@ -249,7 +345,7 @@ __global__ void __launch_bounds__(kThreads) k_inc_count(IncCount a) {
         if (threadIdx.x < 128) {  // entries [lo, hi) hold the run
             const bool up = threadIdx.x >= 64;
             const uint64_t at = wave_upper_item(a.end, 0, a.N2, up ? i1 - 1 : i0);
-            if ((threadIdx.x & 63) == 0) {
+            if (lane == 0) {
                 if (up) s_hi = at + 1;
                 else s_lo = at;
             }
@@ -258,60 +354,77 @@ __global__ void __launch_bounds__(kThreads) k_inc_count(IncCount a) {
         const uint64_t plo = s_lo, phi = s_hi;
         const bool staged = phi - plo <= kStage;
         if (staged)
-            for (uint64_t k = threadIdx.x; k < phi - plo; k += blockDim.x) s_end[k] = a.end[plo + k];
+            for (uint64_t k = threadIdx.x; k < phi - plo; k += blockDim.x) {
+                const uint64_t e = a.end[plo + k] - i0;
+                s_end[k] = (uint16_t)(e < kRun ? e : kRun);
+            }
         __syncthreads();
-        for (uint64_t i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
-            uint64_t p;
-            if (staged) {
-                uint32_t lo = 0, hi = (uint32_t)(phi - plo);
-                while (lo < hi) {
-                    const uint32_t mid = (lo + hi) >> 1;
-                    if (s_end[mid] <= i) lo = mid + 1;
-                    else hi = mid;
+        for (uint64_t ib = i0 + (threadIdx.x & ~63u); ib < i1; ib += blockDim.x) {
+            const uint64_t i = ib + lane;
+            uint32_t u = kNoNode, v = kNoNode, w = 0;
+            bool hit = false;
+            if (i < i1) {
+                uint64_t p;
+                if (staged) {
+                    uint32_t lo = 0, hi = (uint32_t)(phi - plo);
+                    while (lo < hi) {
+                        const uint32_t mid = (lo + hi) >> 1;
+                        if (s_end[mid] <= i - i0) lo = mid + 1;
+                        else hi = mid;
+                    }
+                    p = plo + lo;
+                } else {
+                    p = upper_item(a.end, plo, phi, i);
                 }
-                p = plo + lo;
-            } else {
-                p = upper_item(a.end, plo, phi, i);
+                const uint64_t k = a.ck[p];
+                const uint32_t t = a.ct[p];
+                u = hi32(k);
+                v = lo32(k);
+                const uint32_t su = a.off[u], du = a.off[u + 1] - su, sv = a.off[v], dv = a.off[v + 1] - sv;
+                const uint64_t before = p ? (staged && p > plo ? i0 + s_end[p - 1 - plo] : a.end[p - 1]) : 0;
+                const uint64_t j = i - before;
+                // A: the shorter list (ties: u's), B: the other
+                const bool au = du <= dv;
+                const uint32_t sa = au ? su : sv;
+                const uint32_t sb = au ? sv : su, db = au ? dv : du;
+                if (a.tim[sa + j] < t) {  // (else {x, w} is not yet in any set)
+                    w = lo32(a.key[sa + j]);
+                    // (within a node's run the keys' low words ascend)
+                    const uint32_t* low = (const uint32_t*)a.key + 2 * (uint64_t)sb;
+                    uint32_t q = 0, hi = db;
+                    while (q < hi) {
+                        const uint32_t mid = (q + hi) >> 1;
+                        if (low[2 * (uint64_t)mid] < w) q = mid + 1;
+                        else hi = mid;
+                    }
+                    // triangle {u, v, w} with last edge (u, v)
+                    hit = q < db && low[2 * (uint64_t)q] == w && a.tim[sb + q] < t;
+                }
             }
-            const uint64_t k = a.ck[p];
-            const uint32_t t = a.ct[p];
-            const uint32_t u = hi32(k), v = lo32(k);
-            const uint32_t su = a.off[u], du = a.off[u + 1] - su, sv = a.off[v], dv = a.off[v + 1] - sv;
-            const uint64_t before = p ? (staged && p > plo ? s_end[p - 1 - plo] : a.end[p - 1]) : 0;
-            const uint64_t j = i - before;
-            // A: the shorter list (ties: u's), B: the other
-            const bool au = du <= dv;
-            const uint32_t sa = au ? su : sv;
-            const uint32_t sb = au ? sv : su, db = au ? dv : du, b = au ? v : u;
-            const uint32_t ta = a.tim[sa + j];
-            if (ta >= t) continue;  // {x, w} arrived at or after (u, v): not yet in any set
-            const uint32_t w = lo32(a.key[sa + j]);
-            const uint64_t want = ((uint64_t)b << 32) | w;
-            const uint64_t q = lower_bound64(a.key, sb, (uint64_t)sb + db, want);
-            if (q >= (uint64_t)sb + db || a.key[q] != want || a.tim[q] >= t) continue;
-            // triangle {u, v, w} with last edge (u, v): per group, the processor that stored both
-            // {u, w} and {v, w}, if one did
-            for (uint32_t g = 0; g < a.G; ++g) {
-                const uint64_t* c4 = a.hp + 4 * g;
-                const uint32_t s1 = rept_hash::slot_of(c4, a.m, u, w);
-                const uint32_t s2 = rept_hash::slot_of(c4, a.m, v, w);
-                const uint32_t active = (g + 1 < a.G) ? a.ck_full : a.last_ck;
-                if (s1 != s2 || s1 >= active) continue;
-                const uint32_t proc = g * a.pstride + s1;
-                if (use_hist) atomicAdd(&hist[proc], 1u);
-                else atomicAdd((unsigned long long*)a.global + proc, 1ull);
-                int64_t* row = a.local + (uint64_t)(a.per_proc ? proc : g) * a.n;
-                atomicAdd((unsigned long long*)row + u, 1ull);
-                atomicAdd((unsigned long long*)row + v, 1ull);
-                atomicAdd((unsigned long long*)row + w, 1ull);
+            const uint64_t bal = __ballot(hit);
+            if (hit) {
+                const uint32_t at = queued + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
+                queue.u[at] = u;
+                queue.v[at] = v;
+                queue.w[at] = w;
             }
+            queued += (uint32_t)__popcll(bal);
+            if (queued < 64) continue;
+            wave_fence();
+            count_triangles(a, queue, 64, hist, use_hist, sums, kept);
+            queued -= 64;
+            if (lane < queued) {  // (reads of the upper half, writes of the lower)
+                queue.u[lane] = queue.u[64 + lane];
+                queue.v[lane] = queue.v[64 + lane];
+                queue.w[lane] = queue.w[64 + lane];
+            }
+            wave_fence();
         }
     }
-    if (use_hist) {
-        __syncthreads();
-        for (uint32_t i = threadIdx.x; i < a.c; i += blockDim.x)
-            if (hist[i]) atomicAdd((unsigned long long*)a.global + i, (unsigned long long)hist[i]);
-    }
+    wave_fence();
+    if (queued) count_triangles(a, queue, queued, hist, use_hist, sums, kept);
+    __syncthreads();
+    flush();
 }
 
 __global__ void k_inc_zero64(uint64_t* p, uint64_t words) {
@@ -440,11 +553,9 @@ __global__ void __launch_bounds__(RS_THREADS) k_rs_scatter(const uint64_t* __res
             peers &= one ? bb : ~bb;
         }
         at[r] = wc[w][dig] + (uint32_t)__popcll(peers & below);
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // every lane has read its digit's count
-        __builtin_amdgcn_wave_barrier();
+        wave_fence();  // every lane has read its digit's count
         if (valid && (int)lane == 63 - __clzll(peers)) wc[w][dig] += (uint32_t)__popcll(peers);
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+        wave_fence();
     }
     __syncthreads();
     for (uint32_t d = threadIdx.x; d < 1u << dg.bits; d += RS_THREADS) {
@@ -568,7 +679,7 @@ void rept_inc_accept(IncState& st, uint64_t W) {
     st.flags_clear = true;
 }
 
-hipError_t rept_inc_count(const IncState& st, uint64_t W, const IncCount& base, hipStream_t s) {
+hipError_t rept_inc_count(const IncState& st, uint64_t W, uint64_t items, const IncCount& base, hipStream_t s) {
     (void)hipGetLastError();
     const uint64_t N2 = 2 * W;
     IncCount a = base;
@@ -579,6 +690,14 @@ hipError_t rept_inc_count(const IncState& st, uint64_t W, const IncCount& base, 
     a.ct = st.ctim_b;
     a.end = st.end;
     a.N2 = N2;
-    hipLaunchKernelGGL(k_inc_count, dim3(st.count_blocks), dim3(kThreads), 0, s, a);
+    if (items == 0) return hipSuccess;
+    // Few items are spread over the grid (90k items in runs of 4096 are 22 workgroups: 91 us, in runs of
+    // their threads 18)
+    uint64_t run = (items / st.count_blocks + kCountThreads) / kCountThreads * kCountThreads;
+    if (run > kRun) run = kRun;
+    a.run = (uint32_t)run;
+    const uint64_t runs = (items + run - 1) / run;
+    const uint32_t blocks = runs < st.count_blocks ? (uint32_t)runs : st.count_blocks;
+    hipLaunchKernelGGL(k_inc_count, dim3(blocks), dim3(kCountThreads), 0, s, a);
     return hipGetLastError();
 }

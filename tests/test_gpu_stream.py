@@ -170,3 +170,30 @@ def _fresh(n, k, e):
     v = u + 1 + np.arange(4 * k, dtype=np.int64) // (n - 1)
     keep = np.array([x * n + y not in used and y < n for x, y in zip(u, v)])
     return np.stack([u[keep], v[keep]], 1)[:k].astype(np.uint32)
+
+
+@pytest.mark.parametrize("name", ["sparse", "clique", "hubs"])
+@pytest.mark.parametrize("m,c,per_proc", [(1, 1, False), (2, 16, False), (3, 7, True), (1300, 1100, False)])
+def test_per_edge_count_shapes(cuda, name, m, c, per_proc):
+    """The per-edge count where its stages change: runs with more entries than are staged (a sparse
+    stream), queues that fill in every step (a clique), many large nodes (the table of additions), and
+    more processors than the LDS histogram holds; per chunk against the oracle."""
+    from paper_1811_09136_amd import rept
+    if name == "sparse":
+        n, e = 30000, synth.er(30000, 24000, 3, 4)
+    elif name == "clique":
+        n, e = 150, synth.shuffled(synth.complete(150), 3, flip_seed=4).astype(np.uint32)
+    else:
+        n = 3300
+        y = 300 + np.arange(3000, dtype=np.uint32)
+        e = np.concatenate([np.stack([y, (y * 7 + k * 11) % 300], 1) for k in range(5)] +
+                           [np.stack([np.arange(300), (np.arange(300) + k) % 300], 1) for k in range(1, 40)])
+        e = synth.shuffled(e.astype(np.uint32), 5, flip_seed=6)
+    p = rept.Params(m, c, 21, per_proc)
+    inc = rept.IncrementalStream(n, len(e), len(e), p, cuda, policy="per_edge")
+    cuts = [0, len(e) // 3, len(e) // 3 + 1, len(e) // 2, len(e)]
+    for a, b in zip(cuts[:-1], cuts[1:]):
+        _say(f"per-edge {name} m={m} c={c} per_proc={per_proc} [{a}, {b})")
+        inc.append(rept.to_device_edges(np.ascontiguousarray(e[a:b]), cuda))
+        _check(inc, e[:b], n, p)
+    inc.close()
