@@ -1322,10 +1322,14 @@ __global__ void __launch_bounds__(256) k_prep_one(uint8_t* ctrl, BatchShape shap
 // g; Algorithm 2 as printed, whose counter starts at |N| when g is inserted, counts
 // s L + C(s, 2).  Both go to eta[0][i], eta[1][i]; each edge's share also goes to both of its
 // endpoints in eta_v[0][.], eta_v[1][.] (summed over processors).  Work split as in prepare_job.
+// 16 wavefronts to a chunk: with four, the 489 chunks of 2M edges keep two wavefronts per SIMD in
+// flight on a chain of 16 dependent loads and probes each (149 us, now 121; the rest is the searches
+// for the chunk's first and last node and the atomics of the largest nodes).
+constexpr uint32_t ETA_THREADS = 1024;
 constexpr uint32_t ETA_LDS_PROCS = 512;  // processors accumulated in LDS per workgroup
 constexpr uint32_t ETA_HASH = 1024;      // neighbour shares aggregated per workgroup (open addressing)
 constexpr uint32_t ETA_PROBES = 16;      // probes before a share goes to global memory directly
-__global__ void __launch_bounds__(256) k_eta(const uint32_t* __restrict__ off, const uint32_t* __restrict__ nbr,
+__global__ void __launch_bounds__(ETA_THREADS) k_eta(const uint32_t* __restrict__ off, const uint32_t* __restrict__ nbr,
                                              uint32_t n, const uint16_t* __restrict__ tab, uint32_t gs, uint32_t G,
                                              uint32_t m, uint32_t c, const uint32_t* __restrict__ pairs, uint32_t es,
                                              uint32_t proc0, uint32_t stride,
@@ -1336,8 +1340,8 @@ __global__ void __launch_bounds__(256) k_eta(const uint32_t* __restrict__ off, c
     __shared__ uint32_t hkey[ETA_HASH];                 // neighbour id + 1, 0 = empty
     __shared__ unsigned long long hval[2][ETA_HASH];
     const bool in_lds = c <= ETA_LDS_PROCS;
-    for (uint32_t i = threadIdx.x; i < ETA_LDS_PROCS; i += 256u) acc[0][i] = acc[1][i] = 0ull;
-    for (uint32_t i = threadIdx.x; i < ETA_HASH; i += 256u) {
+    for (uint32_t i = threadIdx.x; i < ETA_LDS_PROCS; i += ETA_THREADS) acc[0][i] = acc[1][i] = 0ull;
+    for (uint32_t i = threadIdx.x; i < ETA_HASH; i += ETA_THREADS) {
         hkey[i] = 0u;
         hval[0][i] = hval[1][i] = 0ull;
     }
@@ -1348,11 +1352,11 @@ __global__ void __launch_bounds__(256) k_eta(const uint32_t* __restrict__ off, c
         for (uint32_t w0 = bf; w0 <= bl; w0 += FILL_NODES) {
             const uint32_t cnt = (bl + 1u - w0) < FILL_NODES ? (bl + 1u - w0) : FILL_NODES;
             __syncthreads();
-            for (uint32_t i = threadIdx.x; i <= cnt; i += 256u) so[i] = ldg(off + w0 + i);
-            for (uint32_t i = threadIdx.x; i < cnt; i += 256u) own[0][i] = own[1][i] = 0ull;
+            for (uint32_t i = threadIdx.x; i <= cnt; i += ETA_THREADS) so[i] = ldg(off + w0 + i);
+            for (uint32_t i = threadIdx.x; i < cnt; i += ETA_THREADS) own[0][i] = own[1][i] = 0ull;
             __syncthreads();
             const uint32_t q0 = so[0] > p0 ? so[0] : p0, q1 = so[cnt] < p1 ? so[cnt] : p1;
-            for (uint32_t p = q0 + threadIdx.x; p < q1; p += 256u) {
+            for (uint32_t p = q0 + threadIdx.x; p < q1; p += ETA_THREADS) {
                 unsigned long long fd = 0, fl = 0;
                 for (uint32_t k = 0; k < G; ++k) {
                     const uint64_t w2 = ldg((const uint64_t*)pairs + (uint64_t)k * es + p);  // (s, L)
@@ -1402,7 +1406,7 @@ __global__ void __launch_bounds__(256) k_eta(const uint32_t* __restrict__ off, c
             }
             __syncthreads();
             if (eta_v) {
-                for (uint32_t i = threadIdx.x; i < cnt; i += 256u) {
+                for (uint32_t i = threadIdx.x; i < cnt; i += ETA_THREADS) {
                     if (own[0][i]) atomicAdd((unsigned long long*)eta_v + w0 + i, own[0][i]);
                     if (own[1][i]) atomicAdd((unsigned long long*)eta_v + n + w0 + i, own[1][i]);
                 }
@@ -1411,7 +1415,7 @@ __global__ void __launch_bounds__(256) k_eta(const uint32_t* __restrict__ off, c
         // the neighbour shares of this run of positions
         __syncthreads();
         if (eta_v) {
-            for (uint32_t i = threadIdx.x; i < ETA_HASH; i += 256u) {
+            for (uint32_t i = threadIdx.x; i < ETA_HASH; i += ETA_THREADS) {
                 const uint32_t key = hkey[i];
                 if (key) {
                     if (hval[0][i]) atomicAdd((unsigned long long*)eta_v + (key - 1u), hval[0][i]);
@@ -1424,7 +1428,7 @@ __global__ void __launch_bounds__(256) k_eta(const uint32_t* __restrict__ off, c
     }
     __syncthreads();
     if (in_lds) {
-        for (uint32_t i = threadIdx.x; i < c; i += 256u) {
+        for (uint32_t i = threadIdx.x; i < c; i += ETA_THREADS) {
             if (acc[0][i]) atomicAdd((unsigned long long*)eta + proc0 + i, acc[0][i]);
             if (acc[1][i]) atomicAdd((unsigned long long*)eta + stride + proc0 + i, acc[1][i]);
         }
@@ -1869,7 +1873,7 @@ hipError_t rept_launch_eta(const rept_graph* g, const JobDev& d, int64_t* eta, i
     uint64_t blocks = (g->E + FILL_CHUNK - 1) / FILL_CHUNK;
     if (blocks > 8192) blocks = 8192;
     if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(k_eta, dim3((uint32_t)blocks), dim3(256), 0, s, g->off, g->nbr, g->n, (const uint16_t*)d.tab,
+    hipLaunchKernelGGL(k_eta, dim3((uint32_t)blocks), dim3(ETA_THREADS), 0, s, g->off, g->nbr, g->n, (const uint16_t*)d.tab,
                        d.gs, d.G, d.m, d.c, (const uint32_t*)d.pairs, d.es, proc0, stride, eta, eta_v);
     return hipGetLastError();
 }
