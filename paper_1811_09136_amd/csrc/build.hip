@@ -45,9 +45,10 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
     return v;
 }
 
-template <typename T>
-__device__ T block_reduce_sum256(T v) {
-    __shared__ T red[SCAN_THREADS / 64];
+// sum and maximum over a workgroup of THREADS threads, valid in thread 0
+template <typename T, int THREADS = SCAN_THREADS>
+__device__ T block_reduce_sum(T v) {
+    __shared__ T red[THREADS / 64];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
@@ -55,13 +56,14 @@ __device__ T block_reduce_sum256(T v) {
     __syncthreads();
     T s = 0;
     if (threadIdx.x == 0)
-        for (int w = 0; w < SCAN_THREADS / 64; ++w) s += red[w];
+        for (int w = 0; w < THREADS / 64; ++w) s += red[w];
     __syncthreads();
-    return s;  // valid in thread 0
+    return s;
 }
 
-__device__ uint32_t block_max256(uint32_t v) {  // valid in thread 0
-    __shared__ uint32_t red[SCAN_THREADS / 64];
+template <int THREADS = SCAN_THREADS>
+__device__ uint32_t block_max(uint32_t v) {
+    __shared__ uint32_t red[THREADS / 64];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
@@ -71,7 +73,7 @@ __device__ uint32_t block_max256(uint32_t v) {  // valid in thread 0
     if (lane == 0) red[wid] = v;
     __syncthreads();
     if (threadIdx.x == 0)
-        for (int w = 1; w < SCAN_THREADS / 64; ++w) v = red[w] > v ? red[w] : v;
+        for (int w = 1; w < THREADS / 64; ++w) v = red[w] > v ? red[w] : v;
     __syncthreads();
     return v;
 }
@@ -376,20 +378,33 @@ __global__ void __launch_bounds__(1024) k_out_count(const OEntry* __restrict__ o
 }
 
 // ---- placement by slices: each bucket's part of the partition is cut into slices of
-// SLICE_ENTRIES entries, one workgroup each (the densest bucket, the top-degree nodes, holds many
+// `slice` entries, one workgroup each (the densest bucket, the top-degree nodes, holds many
 // times the mean).  A slice counts its entries per node of its bucket in LDS; a pass per node
 // sums those counts into the out-degree and, after the scan, turns them into the node's base in
 // each slice (its segment start plus its entries in the bucket's earlier slices); a slice then
 // places its entries with LDS cursors from those bases.  Needs a bucket span of at most DEG_SUB
 // ids (n <= 2^25).
-// At most SLICE_MAX entries a slice (R-MAT scale 24 build: 45.6-46.0 ms at 32768 entries, 45.9 at
-// 65536, 46.9 at 16384, 48.4 at 8192: fewer slices per bucket write fewer per-slice counts and
-// interleave less in each node's segment); fewer where E would leave compute units without a slice
-// (200k edges: the two placements 48 and 50 us with ten slices of 32768, 25 and 7 with slices of 2048).
-constexpr uint32_t SLICE_MAX = 32768, SLICE_MIN = 2048;
-__host__ __device__ inline uint32_t slice_entries(uint64_t E) {
+// At most SLICE_MAX entries a slice: a slice's stores fall all over its bucket's region, so a line
+// of it is written back several times while many slices are in flight, and smaller slices spread a
+// line's stores over less time, against more per-slice counts (20M edges, the two placements with
+// their scans: 1313 us at 32768 entries, 1169 at 16384, 1077 at 8192; stores of 160 MB wrote 603 MB
+// at 32768).  Fewer where E would leave compute units without a slice (200k edges: the two placements
+// 48 and 50 us with ten slices of 32768, 25 and 7 with slices of 2048).  More where the counts would
+// not fit: they take regions that are free while they live (slice_room), or at SLICE_WIDE entries a
+// region of their own.
+constexpr uint32_t SLICE_WIDE = 32768, SLICE_MAX = 8192, SLICE_MIN = 2048;
+__host__ __device__ inline uint64_t slices_at_most(uint64_t E, uint32_t NB, uint32_t slice) {
+    return (E + slice - 1) / slice + NB;
+}
+// bytes free beside the counts' own region: the reverse records (16 per edge) for the out-lists, and
+// the partition's space past the reverse marks (16 per edge less 4, aligned) for the reverse lists
+inline uint64_t slice_room(uint64_t E) { return 12 * E > 256 ? 12 * E - 256 : 0; }
+inline uint32_t slice_entries(uint64_t E, uint32_t NB, uint32_t shift) {
     uint32_t s = SLICE_MIN;
     while (s < SLICE_MAX && (uint64_t)s * 256 < E) s <<= 1;
+    while (s < SLICE_WIDE && slices_at_most(E, NB, s) > slices_at_most(E, NB, SLICE_WIDE) &&
+           (slices_at_most(E, NB, s) << (shift + 2)) > slice_room(E))
+        s <<= 1;
     return s;
 }
 
@@ -443,6 +458,12 @@ __global__ void __launch_bounds__(1024) k_orient_part(const uint2* __restrict__ 
     }
 }
 
+// A placing workgroup's slice: the workgroups of one XCD (every eighth) take neighbouring slices.
+__device__ __forceinline__ uint32_t slice_at(uint32_t slices) {
+    const uint32_t per = (slices + 7u) >> 3, k = blockIdx.x >> 3;
+    return k < per ? (blockIdx.x & 7u) * per + k : slices;
+}
+
 // the slice of workgroup s: its bucket b and entry range [lo, hi); false past the last slice
 __device__ __forceinline__ bool slice_of(uint32_t s, const uint32_t* __restrict__ slice_off,
                                          const uint32_t* __restrict__ boff, uint32_t nblk, uint32_t NB, uint32_t slice,
@@ -494,26 +515,32 @@ __device__ __forceinline__ uint32_t size_class(uint32_t d) {  // 0, 1, 2: medium
 // off[v] from the slices' counts, in one pass over the nodes: v's entries over its bucket's slices
 // (-> dout, if wanted), their exclusive scan (-> off, off[n] = total), and scount[s][v] <- the position
 // of v's first entry of slice s in v's segment.  CLASSIFY: also the segments' size classes and the
-// oriented graph's statistics.  A workgroup takes NODE_TILE nodes, four consecutive ones per thread.
+// oriented graph's statistics.  A workgroup takes NODE_TILE nodes, four consecutive ones per thread,
+// and its SLICE_SETS sets of threads share the slices: the bucket of the top-degree nodes has many
+// (1M nodes and 20M edges: 176 of 8192), and read by one set, eight at a time, they set the launch's
+// length (20M edges, the reverse lists': 199 us by one set, 141 by four).
+constexpr uint32_t SLICE_SETS = 4, SLICE_SCAN_THREADS = SLICE_SETS * SCAN_THREADS;
 template <bool CLASSIFY>
-__global__ void __launch_bounds__(SCAN_THREADS) k_slice_scan(uint32_t* __restrict__ scount,
+__global__ void __launch_bounds__(SLICE_SCAN_THREADS) k_slice_scan(uint32_t* __restrict__ scount,
                                                              const uint32_t* __restrict__ slice_off, uint32_t shift,
                                                              uint32_t n, uint32_t* __restrict__ dout,
                                                              uint32_t* __restrict__ off, Look L, Classes C) {
     static_assert(NODE_ITEMS == 4, "a 16-byte load per slice");
-    // slices read at a time: the bucket of the top-degree nodes has many (1M nodes and 20M edges: 44),
-    // and read one by one they set the launch's length
-    constexpr uint32_t kBatch = 8;
+    __shared__ uint4 part[SLICE_SETS][SCAN_THREADS];
+    __shared__ uint32_t pres[SCAN_THREADS];
+    constexpr uint32_t kBatch = 8;  // slices read at a time
+    const uint32_t set = threadIdx.x / SCAN_THREADS, j = threadIdx.x % SCAN_THREADS;
     const uint32_t t = look_ticket(L);
-    const uint64_t v0 = (uint64_t)t * NODE_TILE + (uint64_t)threadIdx.x * NODE_ITEMS, span = 1ull << shift;
-    uint32_t d[4] = {0u, 0u, 0u, 0u};
+    const uint64_t v0 = (uint64_t)t * NODE_TILE + (uint64_t)j * NODE_ITEMS, span = 1ull << shift;
+    uint32_t d[4] = {0u, 0u, 0u, 0u};  // this set's slices, then all
     uint32_t s0 = 0, s1 = 0;
     uint64_t i = 0;
     if (v0 < n) {  // (the four nodes share a bucket: spans are multiples of four)
         const uint32_t b = (uint32_t)(v0 >> shift);
         i = v0 - ((uint64_t)b << shift);
-        s0 = slice_off[b];
-        s1 = slice_off[b + 1];
+        const uint32_t b0 = slice_off[b], b1 = slice_off[b + 1], share = (b1 - b0 + SLICE_SETS - 1) / SLICE_SETS;
+        s0 = b0 + set * share < b1 ? b0 + set * share : b1;
+        s1 = s0 + share < b1 ? s0 + share : b1;
         for (uint32_t s = s0; s < s1; s += kBatch) {
             uint4 c[kBatch];
 #pragma unroll
@@ -528,14 +555,30 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_slice_scan(uint32_t* __restric
             }
         }
     }
+    part[set][j] = make_uint4(d[0], d[1], d[2], d[3]);
+    __syncthreads();
+    uint32_t run[4] = {0u, 0u, 0u, 0u};  // the sets before this one
+    d[0] = d[1] = d[2] = d[3] = 0u;
+#pragma unroll
+    for (uint32_t q = 0; q < SLICE_SETS; ++q) {
+        if (q == set)
+            for (int r = 0; r < 4; ++r) run[r] = d[r];
+        const uint4 c = part[q][j];
+        d[0] += c.x;
+        d[1] += c.y;
+        d[2] += c.z;
+        d[3] += c.w;
+    }
     uint32_t total;
-    uint32_t pre = block_excl_scan(d[0] + d[1] + d[2] + d[3], total);
+    uint32_t pre = block_excl_scan<uint32_t, SLICE_SCAN_THREADS>(set ? 0u : d[0] + d[1] + d[2] + d[3], total);
     pre += look_back(L, t, total);
-    uint32_t run[4];
+    if (set == 0) pres[j] = pre;
+    __syncthreads();
+    pre = pres[j];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        run[r] = pre;
-        if (v0 + r < n) {
+        run[r] += pre;
+        if (set == 0 && v0 + r < n) {
             off[v0 + r] = pre;
             if (dout) dout[v0 + r] = d[r];
         }
@@ -563,6 +606,7 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_slice_scan(uint32_t* __restric
         __syncthreads();
         unsigned long long sq = 0;
         uint32_t mx = 0, napex = 0, at[4];
+        if (set) d[0] = d[1] = d[2] = d[3] = 0u;  // (class 3)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             sq += (unsigned long long)d[r] * d[r];
@@ -585,9 +629,9 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_slice_scan(uint32_t* __restric
             else if (k == 1) C.large[base[1] + at[r]] = v;
             else if (k == 2) C.medium[base[2] + at[r]] = v;
         }
-        const unsigned long long s = block_reduce_sum256<unsigned long long>(sq);
-        const uint32_t na = block_reduce_sum256<uint32_t>(napex);
-        mx = block_max256(mx);
+        const unsigned long long s = block_reduce_sum<unsigned long long, SLICE_SCAN_THREADS>(sq);
+        const uint32_t na = block_reduce_sum<uint32_t, SLICE_SCAN_THREADS>(napex);
+        mx = block_max<SLICE_SCAN_THREADS>(mx);
         if (threadIdx.x == 0) {
             StatPart& P = C.st->part[t % kStatParts];
             if (mx) atomicMax(&P.max_out, mx);
@@ -611,9 +655,10 @@ __global__ void __launch_bounds__(1024) k_slice_place(const OEntry* __restrict__
     __shared__ uint32_t cur[DEG_SUB];
     uint32_t b;
     uint64_t lo, hi;
-    if (!slice_of(blockIdx.x, slice_off, boff, nblk, NB, slice, b, lo, hi)) return;
+    const uint32_t sl = slice_at(slice_off[NB]);
+    if (!slice_of(sl, slice_off, boff, nblk, NB, slice, b, lo, hi)) return;
     const uint32_t span = 1u << shift, v0 = b << shift;
-    const uint32_t* base = sbase + (uint64_t)blockIdx.x * span;
+    const uint32_t* base = sbase + (uint64_t)sl * span;
     for (uint32_t i = threadIdx.x; i < span; i += blockDim.x) cur[i] = base[i];
     __syncthreads();
     unsigned long long work = 0;
@@ -709,9 +754,10 @@ __global__ void __launch_bounds__(1024) k_rev_place(const uint4* __restrict__ rp
     __shared__ uint32_t cur[DEG_SUB];
     uint32_t b;
     uint64_t lo, hi;
-    if (!slice_of(blockIdx.x, slice_off, boff, nblk, NB, slice, b, lo, hi)) return;
+    const uint32_t sl = slice_at(slice_off[NB]);
+    if (!slice_of(sl, slice_off, boff, nblk, NB, slice, b, lo, hi)) return;
     const uint32_t span = 1u << shift, v0 = b << shift;
-    const uint32_t* base = sbase + (uint64_t)blockIdx.x * span;
+    const uint32_t* base = sbase + (uint64_t)sl * span;
     for (uint32_t i = threadIdx.x; i < span; i += blockDim.x) cur[i] = base[i];
     __syncthreads();
     const uint64_t stride = blockDim.x;
@@ -779,7 +825,7 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scatter(const uint2* __restric
             if (rev) atomicAdd(&rcnt[(uint64_t)b * REV_SHARDS + (a % REV_SHARDS)], 1u);
         }
     }
-    unsigned long long s = block_reduce_sum256<unsigned long long>(work);
+    unsigned long long s = block_reduce_sum<unsigned long long>(work);
     if (threadIdx.x == 0 && s) atomicAdd(&st->part[blockIdx.x % kStatParts].work, s);
 }
 
@@ -854,9 +900,9 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_classify(const uint32_t* __res
         else if (k == 1) large[atomicAdd(&base[1], 1u)] = a;
         else if (k == 2) medium[atomicAdd(&base[2], 1u)] = a;
     }
-    unsigned long long s = block_reduce_sum256<unsigned long long>(sq);
-    uint32_t na = block_reduce_sum256<uint32_t>(napex);
-    mx = block_max256(mx);
+    unsigned long long s = block_reduce_sum<unsigned long long>(sq);
+    uint32_t na = block_reduce_sum<uint32_t>(napex);
+    mx = block_max(mx);
     if (threadIdx.x == 0) {
         StatPart& P = st->part[blockIdx.x % kStatParts];
         if (mx) atomicMax(&P.max_out, mx);
@@ -1342,9 +1388,9 @@ ScratchLayout scratch_layout(uint32_t n, uint64_t E) {
     S.opart = p;  // oriented entries (a, b, t), 12 bytes, partitioned by the bucket of a; later the
                   // reverse marks (4 bytes per edge)
     p += align256((size_t)E * 16);
-    // placement slices (bucket spans of at most DEG_SUB ids): their offsets per bucket and their
-    // per-node counts, then bases
-    const uint64_t smax = sliced ? (E + slice_entries(E) - 1) / slice_entries(E) + D.NB : 0;
+    // placement slices (bucket spans of at most DEG_SUB ids): their offsets per bucket and, of wide
+    // slices, their per-node counts, then bases
+    const uint64_t smax = sliced ? slices_at_most(E, D.NB, SLICE_WIDE) : 0;
     S.slice_off = p;
     p += align256(((size_t)D.NB + 1) * 4);
     S.scount = p;
@@ -1484,23 +1530,24 @@ rept_status rept_build_impl(uint32_t n, const uint32_t* edges, uint64_t E, void*
     // the bucket of its lower endpoint into `opart`, whose out-degrees are counted per bucket
     // with LDS counters (the degree partition's buckets); then the placement in the segments
     uint2* ab = (uint2*)alt;
+    const uint32_t slice = slice_entries(E, D.NB, D.shift);
     hipLaunchKernelGGL(k_orient_hist, dim3(D.nblk), dim3(1024), 0, s, e2, E, n, deg, D.shift, D.NB, D.per_block,
                        ab, bhist);
     if (scan_u32(bhist, (uint64_t)D.NB * D.nblk, look(LOOK_ORIENT), bscan, s) != hipSuccess) return REPT_EDEVICE;
     hipLaunchKernelGGL(k_orient_part, dim3(D.nblk), dim3(1024), 0, s, ab, E, D.shift, D.NB, D.per_block, bscan,
-                       opart, sliced ? slice_off : (uint32_t*)nullptr, slice_entries(E));
+                       opart, sliced ? slice_off : (uint32_t*)nullptr, slice);
     const uint64_t nsh = (uint64_t)n * REV_SHARDS;
     const uint32_t gS = grid_for(nsh, 256, cap);
-    const uint32_t slice = slice_entries(E);
-    const uint64_t smax = (E + slice - 1) / slice + D.NB;
+    const uint64_t smax = slices_at_most(E, D.NB, slice);
+    if (sliced && smax > slices_at_most(E, D.NB, SLICE_WIDE)) scount = (uint32_t*)rrec;
     const uint32_t node_tiles = (uint32_t)(((uint64_t)n + NODE_TILE - 1) / NODE_TILE);
     if (sliced) {  // placement by slices of the partition, LDS cursors
         hipLaunchKernelGGL(k_slice_count<OEntry>, dim3((uint32_t)smax), dim3(1024), 0, s, (const OEntry*)opart, bscan,
                            D.nblk, D.NB,
                            D.shift, slice_off, slice, scount);
-        hipLaunchKernelGGL(k_slice_scan<true>, dim3(node_tiles), dim3(SCAN_THREADS), 0, s, scount, slice_off, D.shift,
+        hipLaunchKernelGGL(k_slice_scan<true>, dim3(node_tiles), dim3(SLICE_SCAN_THREADS), 0, s, scount, slice_off, D.shift,
                            n, dout, off, look(LOOK_OFF), Classes{medium, large, st});
-        hipLaunchKernelGGL(k_slice_place, dim3((uint32_t)smax), dim3(1024), 0, s, opart, bscan, D.nblk, D.NB,
+        hipLaunchKernelGGL(k_slice_place, dim3((uint32_t)(smax + 7) & ~7u), dim3(1024), 0, s, opart, bscan, D.nblk, D.NB,
                            D.shift, slice_off, slice, scount, dout, packed, (uint32_t*)nullptr, st);
     } else {  // wider buckets: out-degrees per bucket in LDS, placement by global cursors
         hipLaunchKernelGGL(k_fill_u32, dim3(gN), dim3(256), 0, s, dout, (uint64_t)n, 0u);
@@ -1538,6 +1585,7 @@ rept_status rept_build_impl(uint32_t n, const uint32_t* edges, uint64_t E, void*
         // the reverse pairs (b, a, t, p) partitioned by the bucket of b into the sort buffers
         // (`packed` and `alt`, 16 bytes per edge together, free after the sorts)
         uint4* rpart = (uint4*)packed;
+        if (scount == (uint32_t*)rrec) scount = (uint32_t*)((uint8_t*)opart + align256((size_t)E * 4));
         hipLaunchKernelGGL(k_rev_hist, dim3(D.nblk), dim3(1024), 0, s, rsrc, nbr, off, n, D.shift, D.NB,
                            D.per_block, bhist);
         if (scan_u32(bhist, (uint64_t)D.NB * D.nblk, look(LOOK_REV), bscan, s) != hipSuccess) return REPT_EDEVICE;
@@ -1545,9 +1593,9 @@ rept_status rept_build_impl(uint32_t n, const uint32_t* edges, uint64_t E, void*
                            D.per_block, bscan, rpart, slice_off, slice);
         hipLaunchKernelGGL(k_slice_count<uint4>, dim3((uint32_t)smax), dim3(1024), 0, s, (const uint4*)rpart, bscan,
                            D.nblk, D.NB, D.shift, slice_off, slice, scount);
-        hipLaunchKernelGGL(k_slice_scan<false>, dim3(node_tiles), dim3(SCAN_THREADS), 0, s, scount, slice_off, D.shift,
+        hipLaunchKernelGGL(k_slice_scan<false>, dim3(node_tiles), dim3(SLICE_SCAN_THREADS), 0, s, scount, slice_off, D.shift,
                            n, (uint32_t*)nullptr, roff, look(LOOK_ROFF), Classes{nullptr, nullptr, nullptr});
-        hipLaunchKernelGGL(k_rev_place, dim3((uint32_t)smax), dim3(1024), 0, s, (const uint4*)rpart, bscan, D.nblk,
+        hipLaunchKernelGGL(k_rev_place, dim3((uint32_t)(smax + 7) & ~7u), dim3(1024), 0, s, (const uint4*)rpart, bscan, D.nblk,
                            D.NB, D.shift, slice_off, slice, scount, off, rrec, rpos);
     }
     hipLaunchKernelGGL(k_apex_hist, dim3(gA), dim3(256), 0, s, off, roff, deg, n, ahist, st);

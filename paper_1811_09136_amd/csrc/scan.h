@@ -4,7 +4,7 @@
 // own, so their workgroups are running and every wait ends.  A tile's word holds its state and its sum
 // together, so no other ordering is needed.  (The three launches of a reduce-then-scan cost a small
 // graph more than the work: a build of 2,000 nodes took seven scans, 21 of its 47 launches.)
-// Workgroups have kScanThreads threads; the words are zero before the launch.
+// Workgroups have kScanThreads threads unless said otherwise; the words are zero before the launch.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -62,10 +62,10 @@ __device__ T look_back(const Look& L, uint32_t t, T sum) {
     return before;
 }
 
-// exclusive scan over the workgroup; `total` in every thread
-template <typename T>
+// exclusive scan over a workgroup of THREADS threads; `total` in every thread
+template <typename T, uint32_t THREADS = kScanThreads>
 __device__ __forceinline__ T block_excl_scan(T v, T& total) {
-    __shared__ T ws[kScanThreads / 64];
+    __shared__ T ws[THREADS / 64];
     const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     T inc = v;
 #pragma unroll
@@ -77,7 +77,7 @@ __device__ __forceinline__ T block_excl_scan(T v, T& total) {
     __syncthreads();
     T base = 0, tot = 0;
 #pragma unroll
-    for (uint32_t i = 0; i < kScanThreads / 64; ++i) {
+    for (uint32_t i = 0; i < THREADS / 64; ++i) {
         if (i < w) base += ws[i];
         tot += ws[i];
     }

@@ -115,3 +115,48 @@ def test_ids_spread_over_two_to_the_26(cuda):
         assert np.array_equal(loc.cpu().numpy(), ol)
         g.close()
         del glob, loc, og, ol
+
+
+@pytest.mark.parametrize("n,E", [
+    (3, 1), (64, 2000), (1024, 2047), (1025, 2049), (4097, 60_000),   # node tiles; slices of 2,048 edges
+    (16384, 90_000), (16385, 90_000),                                 # degrees straight in memory or by buckets
+    (200_000, 300), (300_000, 40_000),                                # more buckets than entries to a slice
+    (30_000, 524_288), (30_000, 524_289),                             # slices of 2,048 and of 4,096 edges
+    (200_000, 2_500_000),                                             # of 8,192, the largest
+])
+def test_build_sizes(cuda, n, E):
+    """Builds at the edges of the tiles and slices, of skewed streams (one bucket of ids holds many times
+    the mean), from the device and from the host; counted against the oracle."""
+    import torch
+    from paper_1811_09136_amd import rept
+    rng = np.random.default_rng(n + E)
+    e = np.zeros((0, 2), np.uint32)
+    while len(e) < E:  # endpoints denser towards low ids, each pair once, in a random order
+        x = (n * rng.random((2 * E + 64, 2)) ** (1.6 if n > 64 else 1.0)).astype(np.int64)
+        x = x[x[:, 0] != x[:, 1]]
+        e = np.concatenate([e.astype(np.int64), x])
+        _, at = np.unique(e.min(1) * n + e.max(1), return_index=True)
+        e = e[np.sort(at)]
+        if n * (n - 1) // 2 < 2 * E:
+            e = synth.complete(n)
+            break
+    e = np.ascontiguousarray(e[:E]).astype(np.uint32)
+    P = rept.Params(4, 6, 13)
+    og, ol = oracle.rept(e, n, 4, 6, 13)
+    _say(f"build n={n} E={len(e)}")
+    g = rept.Graph(rept.to_device_edges(e, cuda), n)
+    glob, loc = g.count(P)
+    torch.cuda.synchronize()
+    assert np.array_equal(glob.cpu().numpy(), og) and np.array_equal(loc.cpu().numpy(), ol)
+    g.close()
+    _say(f"host build n={n} E={len(e)}")
+    pb, sb = rept.rept_query_sizes(n, len(e))
+    pers, scr = (torch.empty(b, dtype=torch.uint8, device=cuda) for b in (pb, sb))
+    sp = torch.cuda.current_stream().cuda_stream
+    h = rept.rept_build_host(n, e, pers.data_ptr(), pb, scr.data_ptr(), sb, sp)
+    wsb = rept.rept_count_workspace_size(h, P)
+    ws = torch.empty(wsb, dtype=torch.uint8, device=cuda)
+    rept.rept_count(h, P, glob.data_ptr(), loc.data_ptr(), ws.data_ptr(), wsb, sp)
+    torch.cuda.synchronize()
+    assert np.array_equal(glob.cpu().numpy(), og) and np.array_equal(loc.cpu().numpy(), ol)
+    rept.rept_destroy(h)
