@@ -432,8 +432,8 @@ def measure_plain(dev, workload: str, steps: int, warmup: int, host_input: bool 
     say(f"{workload}: timed {steps} steps: {ms_per_step:.2f} ms/step, count {sum(count_ms) / len(count_ms):.3f} ms")
 
     # the counting kernel alone, for the roofline: one job whose slot table an earlier launch
-    # wrote (REPT_JOB_TABLE_READY), so a launch runs setup, the output clear and k_count only;
-    # HIP events on the stream the kernels are launched on
+    # wrote (REPT_JOB_TABLE_READY), so a launch runs the preparing kernel (which clears the outputs)
+    # and k_count only; HIP events on the stream the kernels are launched on
     h = rept.rept_build(n, d_edges.data_ptr(), E, persistent.data_ptr(), pbytes, scratch.data_ptr(), sbytes, sp)
     bw = rept.rept_batch_workspace_size(1)
     ws_fill = torch.empty(bw, dtype=torch.uint8, device=dev)

@@ -405,8 +405,9 @@ typedef struct rept_job {
 
 /* Launch shape of the counting kernel; zero fields take the library defaults.  The kernel is
  * persistent: `blocks` workgroups of `threads` threads drain the work queue, first one apex per
- * workgroup (units whose size exceeds wave_cap), then one unit per wavefront.  The LDS
- * footprint of a shape must fit the 160 KB of a compute unit (EINVAL otherwise). */
+ * workgroup (units whose size exceeds wave_cap; one with many lists in parts), then the others,
+ * several to a wavefront.  The LDS footprint of a shape must fit the 160 KB of a compute unit
+ * (EINVAL otherwise). */
 typedef struct rept_tuning {
     uint32_t wave_cap;   /* 8..256: largest unit counted by one wavefront (default 64, or 256 with
                             the wide shape below; halved down to 64 if the light phase's LDS
@@ -417,19 +418,19 @@ typedef struct rept_tuning {
                             with workgroups of up to 512 threads, halved down to 1024 while a
                             workgroup would need more than half the LDS, and below that while
                             it would not fit) */
-    uint32_t b_chunk;    /* 16..1024: neighbour lists staged per chunk by a workgroup (default 512
-                            with 2048-entry chunks, else 128; 1024 with the wide shape; halved
-                            likewise, before block_cap) */
+    uint32_t b_chunk;    /* 16..1024: neighbour lists staged at a time by a workgroup's wavefronts
+                            together, 64 each at most (default 512 with 2048-entry chunks, else
+                            128; 1024 with the wide shape; halved likewise, before block_cap) */
     uint32_t blocks;     /* persistent workgroups (default: as many as fit, up to 4 per CU) */
     uint32_t threads;    /* 64..1024, a multiple of 64 (default 256; the wide shape, taken when
                             the longest list exceeds 1024 entries and none of block_cap and
                             threads is set: 1024, with block_cap 2048, b_chunk 1024,
                             wave_cap 256 and light_tile 16) */
-    uint32_t light_tile; /* 1..64: apexes taken per queue pop by a wavefront (default 8; 16 with
-                            the wide shape) */
+    uint32_t light_tile; /* 1..64: apexes taken per queue pop by a wavefront, at most (default 8;
+                            16 with the wide shape); fewer where they have many lists */
     uint32_t phase_launches; /* 1: both phases in one launch; 2: the light phase (units of at most
-                                wave_cap, one per wavefront) runs as a launch of its own after the
-                                heavy one, its workgroups holding no heavy team area in LDS, so
+                                wave_cap) runs as a launch of its own after the heavy one, in
+                                workgroups of 256 threads that hold no heavy team area in LDS, so
                                 more wavefronts are resident; 0 or 3: that launch on a second
                                 stream of the library's, forked from and joined back to `stream`,
                                 so it runs beside the heavy launch (default) */

@@ -101,8 +101,8 @@ DEFAULT_CANDIDATES = [
     dict(light_tile=2),
     dict(light_tile=32),
     dict(threads=512),
-    dict(threads=512, b_chunk=256),  # R-MAT scale 24: 280 ms against 302 at the default shape
-    dict(phase_launches=1),  # both phases in one launch (the 1M/20M power-law stream: 5.61 ms, 5.72 split)
+    dict(threads=512, b_chunk=256),
+    dict(phase_launches=1),  # both phases in one launch
 ]
 
 
