@@ -51,6 +51,7 @@ constexpr uint32_t kGranHeavy = 16;          // entries of one list walked by on
 constexpr uint32_t kGranLight = 8;           // (light units' lists are shorter)
 constexpr uint32_t kStepHeavy = 4;           // windows of 64 entries loaded together
 constexpr uint32_t kStepLight = 2;           // (a light unit has few, and its registers cost waves)
+constexpr uint32_t kStepEta = 2;             // (with pair counters, four would spill)
 constexpr uint32_t kWalk = 2;                // windows tested between looks at the queue
 constexpr uint32_t kQueue = 64 * (kWalk + 1);  // per-wavefront queue: < 64 left + those windows'
 
@@ -304,12 +305,15 @@ struct JobRegs {
     const uint32_t* rpos;
     int64_t* local;
     const uint16_t* tab;  // slot table of the stored edges, gs slots per edge
-    uint32_t n, G, gs, gp, per_proc, t0, t1, ck, last_ck, pstride, use_hist, mask;
+    uint32_t* pairs;      // Algorithm 2's counters (null: none), es edges to a group
+    uint32_t n, G, gs, gp, per_proc, t0, t1, ck, last_ck, pstride, use_hist, mask, es;
 };
 
 __device__ inline void load_job(const JobDev* __restrict__ j, uint32_t HC, JobRegs& r) {
     r.jd = j;
     r.off = j->off;
+    r.pairs = j->pairs;  // (read per hit: from the job they cost 20M edges 13.0 ms instead of 9.0)
+    r.es = j->es;
     r.nbr = j->nbr;
     r.tim = j->tim;
     r.rrec = j->rrec;
@@ -678,7 +682,7 @@ __device__ __forceinline__ void drain_batch(const JobRegs& J, const TeamView& T,
                 count16(T.cntb, GS * ib + g);
                 count16(T.cntw, GS * k + g);
             }
-            if (ETA && J.jd->pairs) {
+            if (ETA && J.pairs) {
                 // Algorithm 2's per-edge counts (Section III-B): the first two edges gain a
                 // non-last occurrence (s), the last edge a last-edge occurrence (L) when the
                 // same processor stores it.  {a, w} and {a, b} are staged entries, counted in
@@ -691,7 +695,7 @@ __device__ __forceinline__ void drain_batch(const JobRegs& J, const TeamView& T,
                 const uint32_t be = last == 0 ? lw : 1u;  // {a, b}
                 if (we) atomicAdd(&T.ewe[g * T.DW + k], we);
                 if (be) atomicAdd(&T.ebe[g * T.DB + ib], be);
-                uint32_t* cp = J.jd->pairs + 2 * ((uint64_t)g * J.jd->es + p);
+                uint32_t* cp = J.pairs + 2 * ((uint64_t)g * J.es + p);
                 if (last != 2) atomicAdd(cp, 1u);
                 else if (lw) atomicAdd(cp + 1, 1u);
             }
@@ -733,7 +737,7 @@ __device__ __forceinline__ void drain_hits(const JobRegs& J, const TeamView& T, 
 
 // add packed pair counts (s | L << 16) to the stored edge at adjacency position pos, group g
 __device__ __forceinline__ void flush_pair(const JobRegs& J, uint32_t g, uint32_t pos, uint32_t v) {
-    uint32_t* cp = J.jd->pairs + 2 * ((uint64_t)g * J.jd->es + pos);
+    uint32_t* cp = J.pairs + 2 * ((uint64_t)g * J.es + pos);
     if (v & 0xffffu) atomicAdd(cp, v & 0xffffu);
     if (v >> 16) atomicAdd(cp + 1, v >> 16);
 }
@@ -762,7 +766,7 @@ template <bool ETA, bool PACK, uint32_t GS, typename Late>
 __device__ __forceinline__ void walk_items(const JobRegs& J, const TeamView& T, WaveView& V, uint32_t a, uint32_t kbits,
                                            uint32_t fshift, uint32_t bn, uint32_t g_end, const Late& late) {
     constexpr uint32_t kGran = PACK ? kGranLight : kGranHeavy, kWinGran = 64 / kGran;
-    constexpr uint32_t kStep = PACK ? kStepLight : kStepHeavy;
+    constexpr uint32_t kStep = PACK ? kStepLight : (ETA ? kStepEta : kStepHeavy);
     const uint32_t lane = lane_id(), sub = lane % kGran;
     const uint2* const dp = V.desc + lane / kGran;
     uint32_t qn = 0;
@@ -890,7 +894,7 @@ __device__ __forceinline__ void walk_chunk(const JobRegs& J, const TeamView& T, 
             for_counts(T.cntb, J.gp, pos, [&](uint32_t g, uint32_t v) { add_local(J.local, J.n, V.hub, hs, g, b, v); });
         }
         // this chunk's pair counts of the B entries: at most one per W entry each
-        if (ETA && J.jd->pairs)
+        if (ETA && J.pairs)
             for (uint32_t g = 0; g < J.G; ++g) {
                 const uint32_t v = T.ebe[g * T.DB + pos];
                 if (v) flush_pair(J, g, pab, v);
@@ -1030,7 +1034,7 @@ __device__ __forceinline__ void count_apex(const JobRegs& J, const TeamView& T, 
                 walk_chunk<ETA, false>(J, T, V, a, kbits, fshift, b, bo, bd, tb, pab, 0u, lo, hi);
             }
             team_sync<BLOCK>();
-            if (ETA && J.jd->pairs) {
+            if (ETA && J.pairs) {
                 for (uint32_t x = tid; x < G * wn; x += nt) {
                     const uint32_t g = x / wn, i = x - g * wn;
                     const uint32_t v = T.ewe[g * T.DW + i];
@@ -1186,7 +1190,7 @@ __device__ __forceinline__ void count_pack(const JobRegs& J, const TeamView& T, 
                     add_local(J.local, J.n, V.hub, hs, g, w, v);
                     atomicAdd(&T.uown[g * kPack + u], v);
                 });
-            if (ETA && J.jd->pairs)  // a W entry gains at most one per list of its unit: 16 bits each suffice
+            if (ETA && J.pairs)  // a W entry gains at most one per list of its unit: 16 bits each suffice
                 for (uint32_t g = 0; g < G; ++g) {
                     const uint32_t v = T.ewe[g * T.DW + i];
                     if (v) flush_pair(J, g, T.us[u] + (i - T.uw0[u]), v);
