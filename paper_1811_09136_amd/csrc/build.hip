@@ -1606,8 +1606,7 @@ rept_status rept_build_impl(uint32_t n, const uint32_t* edges, uint64_t E, void*
     if (hipGetLastError() != hipSuccess) return REPT_EDEVICE;
 
     BuildStats hs;
-    if (hipMemcpyAsync(&hs, st, sizeof(hs), hipMemcpyDeviceToHost, s) != hipSuccess) return REPT_EDEVICE;
-    if (hipStreamSynchronize(s) != hipSuccess) return REPT_EDEVICE;
+    if (rept_read_back(&hs, st, sizeof(hs), s) != hipSuccess) return REPT_EDEVICE;
     if (hs.flags & RF_RANGE) return REPT_ERANGE;
     if (hs.flags & RF_SELFLOOP) return REPT_ESELFLOOP;
     if (hs.flags & RF_DUP) return REPT_EDUP;

@@ -215,6 +215,9 @@ uint32_t rept_count_lds(uint32_t threads, uint32_t wave_cap, uint32_t block_cap,
 uint32_t rept_count_blocks_per_cu(uint32_t threads, uint32_t lds_bytes, bool eta, uint32_t phases);
 uint32_t rept_num_cus();
 
+// copy `bytes` from the device and wait for it
+hipError_t rept_read_back(void* dst, const void* src, size_t bytes, hipStream_t stream);
+
 // ---- incremental streaming (stream.hip) ------------------------------------------------------
 // Device state of an incrementally built stream: the adjacency of the edges seen so far, both
 // directions, keys (x << 32 | y) sorted ascending with arrival times beside them (double

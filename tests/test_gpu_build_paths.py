@@ -160,3 +160,32 @@ def test_build_sizes(cuda, n, E):
     torch.cuda.synchronize()
     assert np.array_equal(glob.cpu().numpy(), og) and np.array_equal(loc.cpu().numpy(), ol)
     rept.rept_destroy(h)
+
+
+def test_builds_from_many_threads(cuda):
+    """More builds at a time than there are slots for their results, each thread on a stream of its own."""
+    import threading
+    import torch
+    from paper_1811_09136_amd import rept
+    streams = [synth.er(400, 1500 + 10 * k, k, k + 1) for k in range(24)]
+    devs = [rept.to_device_edges(e, cuda) for e in streams]
+    torch.cuda.synchronize()
+    got = [None] * len(streams)
+
+    def run(k):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(3):
+                g = rept.Graph(devs[k], 400)
+                got[k] = (g.info.num_edges, g.info.num_apex, g.info.max_out_degree, g.info.oriented_work)
+                g.close()
+
+    threads = [threading.Thread(target=run, args=(k,)) for k in range(len(streams))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    _say("builds from 24 threads")
+    for k, d in enumerate(devs):
+        g = rept.Graph(d, 400)
+        assert got[k] == (g.info.num_edges, g.info.num_apex, g.info.max_out_degree, g.info.oriented_work)
+        g.close()
