@@ -729,9 +729,11 @@ template <bool ETA, bool PACK, uint32_t GS>
 __device__ __forceinline__ void drain_hits(const JobRegs& J, const TeamView& T, WaveView& V, uint32_t a, uint32_t kbits,
                                            HitBatch<GS>& D, std::integral_constant<bool, PACK>) {
     drain_batch<ETA, PACK, GS>(J, T, V, a, kbits, D);
-    const uint32_t h = V.hits + D.n;
-    if (h >= kHistFlushHits) flush_hist_now(J, V);
-    else V.hits = h;
+    if (J.use_hist) {  // (without one, c is larger than the histogram: there is nothing to flush)
+        const uint32_t h = V.hits + D.n;
+        if (h >= kHistFlushHits) flush_hist_now(J, V);
+        else V.hits = h;
+    }
     D.n = 0;
 }
 
