@@ -230,7 +230,7 @@ void plan_tiles(BatchHeader* h, JobDev* jobs, const GraphOf& graph_of, const rep
     uint64_t lists = 0;
     for (uint32_t j = 0; j < h->njobs; ++j) lists += graph_of(j)->E + graph_of(j)->num_rev;
     const uint32_t lblocks = h->split ? h->light_blocks : h->blocks;
-    const uint32_t lwaves = lblocks * ((h->split ? kLightThreads : h->threads) / 64);
+    const uint64_t lwaves = (uint64_t)lblocks * ((h->split ? kLightThreads : h->threads) / 64);
     // Lists per tile: a queue that hands each workgroup (wavefront) one tile ends unevenly, but a part
     // of a unit stages the unit's list again and updates the counters of its entries again, most of
     // them hubs' (one 64-byte line of counters takes an update every 12 ns).  2M-edge power law,

@@ -1778,6 +1778,11 @@ hipError_t set_attrs() {
 // table is in `ws` already
 hipError_t launch_common(uint8_t* ws, const BatchHeader& h, const JobDev* one, hipStream_t s) {
     (void)hipGetLastError();  // launch errors below are this call's own
+    // a grid of 2^32 threads or more cannot be launched: refused before anything is enqueued (below it
+    // the kernel's counts of workgroups and wavefronts fit 32 bits)
+    auto fits = [](uint32_t blocks, uint32_t threads) { return (uint64_t)blocks * threads <= UINT32_MAX; };
+    if (!fits(h.blocks, h.threads) || (h.split && !fits(h.light_blocks, kLightThreads)))
+        return report(hipErrorInvalidConfiguration, "counting kernel grid");
     hipError_t e = set_attrs();
     if (e != hipSuccess) return e;
     BatchHeader* hdr = (BatchHeader*)ws;
