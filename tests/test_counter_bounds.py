@@ -8,9 +8,8 @@ stream's exact tau is 10,286,644,549).  The bounds, read from the kernel sources
   hits, so a counter never exceeds kHistFlushHits - 1 + kQueue;
 * the incremental count's per-workgroup histogram gains at most one per item; it is flushed
   before the items since the last flush would pass 2^31, with at most kRun items per run;
-* a staged entry's local counter gains at most one per list walked against it (fewer than
-  2 * 2^31 lists: streams hold fewer than 2^31 edges) or per entry of its table chunk (<= 4096),
-  and a unit's own count is summed in 64 bits: for a light unit in one 32-bit pass when the
+* a staged entry's local counters have 16 bits (test_counter_widths.py), and a unit's own count,
+  their sum, is taken in 64 bits: for a light unit in one 32-bit pass when the
   chunk's W entries times the unit's lists is below 2^32 (each W entry gains at most one per
   list), else in pieces of 26, 26 and 12 bits whose 64-lane sums stay below 2^32.
 """
