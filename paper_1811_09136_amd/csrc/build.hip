@@ -1427,8 +1427,8 @@ uint32_t grid_for(uint64_t items, uint32_t threads, uint32_t cap) {
 }  // namespace
 
 // Where a host-resident stream is staged in the persistent buffer: the reverse records' region
-// (16 bytes per edge), which the build writes only in the segment sorts, after every pass that
-// reads the stream.
+// (16 bytes per edge).  The stream is read for the last time by k_orient_hist; from k_slice_count on the
+// slices' counts may overwrite it (rept_build_impl's scount), and later the records do.
 size_t rept_host_stage_offset(uint32_t n, uint64_t E) { return persistent_layout(n, E).rrec; }
 
 void rept_sizes_impl(uint32_t n, uint64_t E, size_t* persistent, size_t* scratch) {
@@ -1539,6 +1539,7 @@ rept_status rept_build_impl(uint32_t n, const uint32_t* edges, uint64_t E, void*
     const uint64_t nsh = (uint64_t)n * REV_SHARDS;
     const uint32_t gS = grid_for(nsh, 256, cap);
     const uint64_t smax = slices_at_most(E, D.NB, slice);
+    // (a host-resident stream lies there: k_orient_hist, before this, was the last pass to read it)
     if (sliced && smax > slices_at_most(E, D.NB, SLICE_WIDE)) scount = (uint32_t*)rrec;
     const uint32_t node_tiles = (uint32_t)(((uint64_t)n + NODE_TILE - 1) / NODE_TILE);
     if (sliced) {  // placement by slices of the partition, LDS cursors

@@ -224,7 +224,7 @@ hipError_t rept_read_back(void* dst, const void* src, size_t bytes, hipStream_t 
 // buffered: the merge writes the other copy), node offsets, and the chunk work space.
 struct IncState {
     uint32_t n;
-    uint32_t end_bit;  // radix-sort bits of a key: 32 + bit length of n - 1
+    uint32_t id_bits;  // bit length of n - 1 (at least 1): the radix sort's bits per id
     uint64_t T;        // edges appended so far
     int cur;           // the current adjacency copy
     uint64_t* key[2];
@@ -267,8 +267,8 @@ struct IncCount {
     uint32_t ck_full, last_ck, pstride, per_proc;  // processor map as in JobDev
     uint64_t hp[4 * REPT_GMAX];
 };
-// temporary bytes for sorting the 2W `entries` of a chunk and for the scans (end_bit as in IncState)
-size_t rept_inc_sort_temp_bytes(uint64_t entries, uint32_t end_bit);
+// temporary bytes for sorting the 2W `entries` of a chunk and for the scans
+size_t rept_inc_sort_temp_bytes(uint64_t entries);
 hipError_t rept_inc_zero64(void* p, uint64_t words, hipStream_t stream);
 // steps 1-4 of an append: keys, sort, merge into the other copy, validation word, work items (one per
 // entry of the shorter list of each chunk edge's endpoints, their total beside the validation word);

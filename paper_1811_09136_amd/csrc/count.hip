@@ -1617,7 +1617,7 @@ __global__ void __launch_bounds__(phases == 2u ? kLightThreads : 1024u, phases =
     }
     __syncthreads();  // the union area changes owners
 
-    // phase 2: short lists, one apex per wavefront
+    // phase 2: short lists, several apexes to a wavefront
     if (phases & 2u) {
         uint8_t* const mine = uni + wid * (L.lw.bytes + L.lb.bytes + L.lu.bytes);
         TeamView T = team_view(mine, mine + L.lw.bytes, L.lw, L.lb, DL, wave_lists(DLB, 1));

@@ -1,4 +1,5 @@
-// Single-launch scans: a workgroup takes the next tile by a ticket, sums it, publishes the sum and
+// Single-launch scans with decoupled look-back (Merrill and Garland, "Single-pass Parallel Prefix Scan
+// with Decoupled Look-back", 2016): a workgroup takes the next tile by a ticket, sums it, publishes the sum and
 // adds up the sums of the tiles before it (wavefront 0, 64 tiles at a look) until it meets one that
 // has published its inclusive sum.  It only ever waits for tiles whose tickets were drawn before its
 // own, so their workgroups are running and every wait ends.  A tile's word holds its state and its sum

@@ -609,10 +609,7 @@ constexpr uint64_t kRankEdges = 8192;
 
 // ---------------------------------------------------------------------------- launchers ----
 
-size_t rept_inc_sort_temp_bytes(uint64_t entries, uint32_t end_bit) {
-    (void)end_bit;
-    return sort_temp(entries).total;
-}
+size_t rept_inc_sort_temp_bytes(uint64_t entries) { return sort_temp(entries).total; }
 
 hipError_t rept_inc_zero64(void* p, uint64_t words, hipStream_t s) {
     (void)hipGetLastError();
@@ -633,7 +630,7 @@ hipError_t rept_inc_prepare(IncState& st, const uint32_t* edges, uint64_t W, uin
     if (W <= kRankEdges) {
         hipLaunchKernelGGL(k_inc_rank, dim3((uint32_t)((N2 + 63) / 64)), dim3(kRankThreads), 0, s, (const uint2*)edges, a);
     } else {
-        const uint32_t id_bits = st.end_bit - 32, passes = (2 * id_bits + kDigit - 1) / kDigit;
+        const uint32_t id_bits = st.id_bits, passes = (2 * id_bits + kDigit - 1) / kDigit;
         uint64_t *src_k = st.ckey_b, *dst_k = st.ckey_a;  // the last pass ends in b
         uint32_t *src_t = st.ctim_b, *dst_t = st.ctim_a;
         if (passes & 1u) {
