@@ -449,7 +449,8 @@ rept_status rept_batch_workspace_size(uint32_t njobs, size_t* bytes);
  * rept_batch_launch(workspace) enqueued on `stream` after this call run this batch (a launch on
  * another stream must first wait for `stream`), and a launch still reading the workspace's
  * previous table on `stream` finishes before the copy overwrites it.  The job table holds only
- * device pointers and sizes, so a launch can be captured into a HIP graph and replayed.
+ * device pointers and sizes, so a launch can be captured into a HIP graph and replayed, also after
+ * the workspace is prepared again for as many jobs of the same launch shape (the replay runs those).
  * Errors: EINVAL, ENOTSUP, ENOMEM (workspace too small, or no pinned staging memory), EDEVICE.
  */
 rept_status rept_batch_prepare(const rept_job* jobs, uint32_t njobs, const rept_tuning* tuning,

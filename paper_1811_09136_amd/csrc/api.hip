@@ -67,6 +67,7 @@ size_t table_bytes(const rept_graph* g, const rept_params* p) {
 
 struct Shape {
     BatchHeader hdr;
+    uint32_t blocks, light_blocks;  // its grids before they were fitted to the jobs' tiles
 };
 std::mutex g_mu;
 std::unordered_map<void*, Shape> g_shapes;  // prepared batch workspaces -> launch shape
@@ -1124,6 +1125,7 @@ rept_status rept_batch_prepare(const rept_job* jobs, uint32_t njobs, const rept_
     if (st != REPT_OK) return st;
     h.any_fill = any_fill ? 1u : 0u;
     h.fill_edges = fill_edges > UINT32_MAX ? UINT32_MAX : (uint32_t)fill_edges;
+    const uint32_t blocks = h.blocks, light_blocks = h.light_blocks;
     plan_tiles(&h, hj, [jobs](uint32_t j) { return jobs[j].graph; }, tuning);
     memcpy(host, &h, sizeof(h));
     // stream-ordered: launches enqueued on `stream` after this call see the table; the staging
@@ -1133,17 +1135,26 @@ rept_status rept_batch_prepare(const rept_job* jobs, uint32_t njobs, const rept_
     if (e != hipSuccess) return REPT_EDEVICE;
     slot->pending = true;
     std::lock_guard<std::mutex> lk(g_mu);
-    g_shapes[workspace] = Shape{h};
+    g_shapes[workspace] = Shape{h, blocks, light_blocks};
     return REPT_OK;
 }
 
 rept_status rept_batch_launch(void* workspace, void* stream) {
-    BatchHeader h;
+    Shape shape;
     {
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_shapes.find(workspace);
         if (it == g_shapes.end()) return REPT_EINVAL;
-        h = it->second.hdr;
+        shape = it->second;
+    }
+    BatchHeader& h = shape.hdr;
+    // A graph that records this launch may be replayed after the workspace is prepared for other jobs,
+    // whose tiles are not known here: both phases are recorded, on the whole grids.
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing((hipStream_t)stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusActive) {
+        h.heavy_total = h.light_total = 1;
+        h.blocks = shape.blocks;
+        h.light_blocks = shape.light_blocks;
     }
     if (rept_launch_batch(workspace, h, (hipStream_t)stream) != hipSuccess) return REPT_EDEVICE;
     return REPT_OK;
