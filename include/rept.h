@@ -421,8 +421,9 @@ typedef struct rept_tuning {
     uint32_t b_chunk;    /* 16..1024: neighbour lists staged at a time by a workgroup's wavefronts
                             together, 64 each at most (default 512 with 2048-entry chunks, else
                             128; 1024 with the wide shape; halved likewise, before block_cap) */
-    uint32_t blocks;     /* persistent workgroups (default: as many as fit, up to 4 per CU); the launch
-                            is refused (EDEVICE) if blocks times threads exceeds 2^32 - 1 */
+    uint32_t blocks;     /* persistent workgroups (default: as many as fit, up to 4 per CU); a launch
+                            of 2^32 threads or more (256 per workgroup in a light phase of its own)
+                            is refused with EDEVICE */
     uint32_t threads;    /* 64..1024, a multiple of 64 (default 256; the wide shape, taken when
                             the longest list exceeds 1024 entries and none of block_cap and
                             threads is set: 1024, with block_cap 2048, b_chunk 1024,
