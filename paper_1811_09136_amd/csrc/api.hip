@@ -1149,9 +1149,12 @@ rept_status rept_batch_launch(void* workspace, void* stream) {
     }
     BatchHeader& h = shape.hdr;
     // A graph that records this launch may be replayed after the workspace is prepared for other jobs,
-    // whose tiles are not known here: both phases are recorded, on the whole grids.
+    // whose tiles are not known here: both phases are recorded, on the whole grids.  If one of them has
+    // nothing to do by now, they follow each other on `stream`: a replay of one job of 20k edges takes
+    // 37 us, 54 with the empty phase on the second stream (34 without it).
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing((hipStream_t)stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusActive) {
+        if (!h.heavy_total || !h.light_total) h.split_streams = 0;
         h.heavy_total = h.light_total = 1;
         h.blocks = shape.blocks;
         h.light_blocks = shape.light_blocks;
